@@ -320,8 +320,7 @@ uint64_t hamming_planes_words(uint64_t n_cw, int r);
  * Decode n_cw codewords given in the plane layout (n_cw at most
  * 2^37 - 2^13 per call, the reach of one launch).
  *   planes     : device, n planes of plane_words 64-bit words (8-byte aligned).
- *   data_out   : device, hamming_data_bytes(n_cw, r) bytes (8-byte aligned;
- *                16-byte alignment enables vector stores).
+ *   data_out   : device, hamming_data_bytes(n_cw, r) bytes (8-byte aligned).
  *   errpos_out : device, n_cw bytes, or NULL.
  * Returns HAMMING_OK, HAMMING_EINVAL, HAMMING_EALIGN, HAMMING_ERANGE (n_cw
  * too large, or plane_words below ceil(n_cw/64)) or HAMMING_EDEVICE.

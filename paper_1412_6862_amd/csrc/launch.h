@@ -7,9 +7,7 @@
 namespace hm {
 
 // Kernel flag bits, decided on the host from pointer alignment.
-constexpr uint32_t kFlagIn16 = 1u;    // codeword input is 16-byte aligned
 constexpr uint32_t kFlagEpVec = 2u;   // errpos output is aligned to U bytes
-constexpr uint32_t kFlagOut16 = 4u;   // message output is 16-byte aligned
 
 struct DecodeLaunch {
     int r;

@@ -41,55 +41,98 @@ struct PlaneShape {
     static constexpr int N = Code<R>::N;
     static constexpr int K = Code<R>::K;
     static constexpr int NB = (K + 31) / 32;                     // 32-row transpose blocks
-    static constexpr int WAVES = R == 7 ? 1 : (R == 6 ? 2 : 4);   // waves per block (LDS bound)
-    static constexpr int MSG_DW = 64 * K;                         // staged message dwords per wave
-    static constexpr int EP_DW = 64 * 8;                          // staged errpos dwords per wave
-    static constexpr int LDS_DW = MSG_DW + EP_DW;
+    static constexpr int WAVES = 4;                              // waves per block
+    // Lanes whose messages are staged at once.  A lane produces K dwords; a
+    // buffer for all 64 lanes costs 14.3 KB per wave at r = 6 and 30 KB at
+    // r = 7 and left 9 and 5 waves on a CU, so the long messages go out in
+    // rounds of 32 and 16 lanes through 7.1 and 7.5 KB (r = 6, 2^26 codewords:
+    // 195 -> 184 us, r = 7, 2^25: 219 -> 195 us, 5.8 and 5.5 TB/s).
+    static constexpr int LANES = R == 7 ? 16 : (R == 6 ? 32 : 64);
+    static constexpr int MSG_DW = LANES * K;
+    static constexpr int EP_DW = 64 * 8;                          // errpos dwords per wave, staged first
+    static constexpr int LDS_DW = MSG_DW > EP_DW ? MSG_DW : EP_DW;
+    static_assert(MSG_DW % 4 == 0 && LDS_DW % 4 == 0, "staged messages must be whole 16-byte vectors");
 };
 
 // In-place transpose of a 32x32 bit matrix: bit c of row i moves to bit i of
-// row c.  Stage j swaps, for rows k and k+j (bit j of k clear), the columns
-// with bit j set in row k against the columns with bit j clear in row k+j.
+// row c.  Stage j exchanges, for rows k and k+j (bit j of k clear), the
+// columns with bit j set in row k against the columns with bit j clear in row
+// k+j.  Stages 16 and 8 move whole bytes (one byte permute per row), the
+// others take a shift and a bit-field insert per row: 256 VALU instructions
+// against 480 for the usual masked-difference form of every stage.
 __device__ __forceinline__ void transpose32(uint32_t* A)
 {
-    constexpr uint32_t masks[5] = {0x0000FFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
 #pragma unroll
-    for (int st = 0; st < 5; ++st) {
-        const int j = 16 >> st;
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t x = A[k], y = A[k + 16];
+        A[k] = __builtin_amdgcn_perm(y, x, 0x05040100u);        // low halves of x, y
+        A[k + 16] = __builtin_amdgcn_perm(y, x, 0x07060302u);   // high halves
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+        if (k & 8) continue;
+        const uint32_t x = A[k], y = A[k + 8];
+        A[k] = __builtin_amdgcn_perm(y, x, 0x06020400u);        // even bytes of x, y interleaved
+        A[k + 8] = __builtin_amdgcn_perm(y, x, 0x07030501u);    // odd bytes
+    }
+    constexpr uint32_t masks[3] = {0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+#pragma unroll
+    for (int st = 0; st < 3; ++st) {
+        const int j = 4 >> st;
         const uint32_t m = masks[st];
 #pragma unroll
         for (int k = 0; k < 32; ++k) {
             if (k & j) continue;
-            const uint32_t t = ((A[k] >> j) ^ A[k + j]) & m;
-            A[k + j] ^= t;
-            A[k] ^= t << j;
+            const uint32_t x = A[k], y = A[k + j];
+            A[k] = (x & m) | ((y << j) & ~m);
+            A[k + j] = ((x >> j) & m) | (y & ~m);
         }
     }
 }
 
-template <int R>
+// Blocks of the decode that each XCD takes in turn: neighbouring waves read
+// neighbouring 256-byte pieces of every plane, and planes that do not start on
+// a cache line share lines between them (2^24 codewords, slices of 16 against
+// 1: r = 5 26-28 against 30-32 us, r = 6 48-53 against 57-61 us).
+constexpr uint32_t kPlanesXcdChunk = 16;
+
+// Planes of at most this many bytes are read with ordinary loads, larger ones
+// with nontemporal loads.  Planes are usually decoded right after they were
+// written, and up to a quarter of the 256 MB Infinity Cache they are still
+// there: r = 5, 2^24 codewords (62 MiB) 22.4 against 26-27 us, r = 3, 2^26
+// codewords (56 MiB) 24.4 against 28 us.  When they are not, ordinary loads
+// cost 0-8% at these sizes (27.4 against 26.6 us, 30.8 against 28.6 us);
+// beyond, nontemporal ones are 3-10% faster either way (r = 6, 2^24: 48
+// against 52-55 us).
+constexpr uint64_t kPlanesCachedBytes = uint64_t(64) << 20;
+
+template <int R, bool NT>
 __global__ __launch_bounds__(64 * PlaneShape<R>::WAVES) void decode_planes_kernel(
     const uint32_t* __restrict__ planes, uint64_t plane_dwords, uint64_t n_cw, uint32_t* __restrict__ data,
     uint64_t data_dwords, uint8_t* __restrict__ errpos, uint32_t flags)
 {
     using S = PlaneShape<R>;
     constexpr int N = S::N, K = S::K, NB = S::NB;
-    __shared__ uint32_t lds[S::WAVES * S::LDS_DW];
+    __shared__ u32x4 lds_raw[S::WAVES * S::LDS_DW / 4];
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t wave = uint64_t(blockIdx.x) * S::WAVES + wib;
+    const uint64_t wave = uint64_t(xcd_block(blockIdx.x, gridDim.x, kPlanesXcdChunk)) * S::WAVES + wib;
     const uint64_t groups = (n_cw + 31) / 32;
     if (wave * 64 >= groups) return;
     const uint64_t g = wave * 64 + lane;
-    uint32_t* Mw = lds + wib * S::LDS_DW;
-    uint32_t* Ew = Mw + S::MSG_DW;
+    uint32_t* buf = reinterpret_cast<uint32_t*>(lds_raw) + wib * S::LDS_DW;
 
     // a1: one dword of every plane = 32 codewords, bit-sliced
     uint32_t P[N];
     if (g < groups) {
         const uint32_t* src = planes + g;
 #pragma unroll
-        for (int p = 0; p < N; ++p) P[p] = __builtin_nontemporal_load(src + uint64_t(p) * plane_dwords);
+        for (int p = 0; p < N; ++p) {
+            if constexpr (NT)
+                P[p] = __builtin_nontemporal_load(src + uint64_t(p) * plane_dwords);
+            else
+                P[p] = src[uint64_t(p) * plane_dwords];
+        }
         if (g == groups - 1 && (n_cw & 31u)) {
             const uint32_t valid = (1u << (n_cw & 31u)) - 1u;
 #pragma unroll
@@ -111,13 +154,32 @@ __global__ __launch_bounds__(64 * PlaneShape<R>::WAVES) void decode_planes_kerne
         s[j] = x;
     }
 
-    // a3: errpos bytes, codeword c = byte c%4 of dword c/4
+    // a3: errpos bytes, codeword c = byte c%4 of dword c/4, out through the
+    // wave's buffer before the messages need it
+    if (errpos) {
 #pragma unroll
-    for (int d = 0; d < 8; ++d) {
-        uint32_t e = 0;
+        for (int d = 0; d < 8; ++d) {
+            uint32_t e = 0;
 #pragma unroll
-        for (int j = 0; j < R; ++j) e |= ((((s[j] >> (4 * d)) & 0xFu) * 0x00204081u) & 0x01010101u) << j;
-        Ew[lane * 8 + d] = e;
+            for (int j = 0; j < R; ++j) e |= ((((s[j] >> (4 * d)) & 0xFu) * 0x00204081u) & 0x01010101u) << j;
+            buf[lane * 8 + d] = e;
+        }
+        wave_sync();
+        const uint64_t e0 = wave * 2048;
+        const bool ev = (flags & kFlagEpVec) != 0;
+#pragma unroll
+        for (uint32_t q = 0; q < 2; ++q) {
+            const uint32_t v = lane + 64 * q;
+            const uint64_t at = e0 + 16ull * v;
+            if (at >= n_cw) break;
+            const u32x4 x = *reinterpret_cast<const u32x4*>(buf + 4 * v);
+            if (ev && at + 16 <= n_cw) {
+                __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(errpos + at));
+            } else {
+                for (int i = 0; i < 16 && at + i < n_cw; ++i) errpos[at + i] = uint8_t(x[i / 4] >> (8 * (i % 4)));
+            }
+        }
+        wave_sync();
     }
 
     // a4: correction masks from minterms of the low and high checksum planes
@@ -157,28 +219,28 @@ __global__ __launch_bounds__(64 * PlaneShape<R>::WAVES) void decode_planes_kerne
             X[m] = 0;
         }
     }
+    uint32_t out[K];                 // the lane's 32 messages in stream order
     if constexpr (K == 4) {
         // Hamming(7,4): output dword w holds codewords 8w..8w+7, four bits
         // each; spread byte w of message plane m to every fourth bit
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            uint32_t out = 0;
+            out[w] = 0;
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 uint32_t x = (X[m] >> (8 * w)) & 0xFFu;
                 x = (x | (x << 12)) & 0x000F000Fu;
                 x = (x | (x << 6)) & 0x03030303u;
                 x = (x | (x << 3)) & 0x11111111u;
-                out |= x << m;
+                out[w] |= x << m;
             }
-            Mw[lane * K + w] = out;
         }
     } else {
 #pragma unroll
         for (int b = 0; b < NB; ++b) transpose32(X + 32 * b);
 
         // a6: codeword c's message bits [32b, 32b+32) are X[32b + c]; append
-        // them in stream order (c*K + 32b) and emit each completed dword
+        // them in stream order (c*K + 32b), completing one dword after another
         uint32_t acc = 0;
         int filled = 0, wout = 0;
 #pragma unroll
@@ -189,7 +251,7 @@ __global__ __launch_bounds__(64 * PlaneShape<R>::WAVES) void decode_planes_kerne
                 const int len = (K - 32 * b) < 32 ? (K - 32 * b) : 32;
                 acc |= filled ? (v << filled) : v;
                 if (filled + len >= 32) {
-                    Mw[lane * K + wout] = acc;
+                    out[wout] = acc;
                     ++wout;
                     acc = filled ? (v >> (32 - filled)) : 0u;
                     filled = filled + len - 32;
@@ -199,60 +261,140 @@ __global__ __launch_bounds__(64 * PlaneShape<R>::WAVES) void decode_planes_kerne
             }
         }
     }
-    wave_sync();
 
-    // coalesced stores of the wave's message dwords and errpos bytes
-    const uint64_t dw0 = wave * 64 * K;
-    const bool out16 = (flags & kFlagOut16) != 0;
-    for (uint32_t v = lane; v < 16u * K; v += 64) {
-        const uint64_t at = dw0 + 4ull * v;
-        if (at >= data_dwords) break;
-        const u32x4 x = *reinterpret_cast<const u32x4*>(Mw + 4 * v);
-        if (out16 && at + 4 <= data_dwords) {
-            __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(data + at));
-        } else {
-            for (int q = 0; q < 4 && at + q < data_dwords; ++q) data[at + q] = x[q];
-        }
-    }
-    if (errpos) {
-        const uint64_t e0 = wave * 2048;
-        const bool ev = (flags & kFlagEpVec) != 0;
-        for (uint32_t v = lane; v < 128; v += 64) {
-            const uint64_t at = e0 + 16ull * v;
-            if (at >= n_cw) break;
-            const u32x4 x = *reinterpret_cast<const u32x4*>(Ew + 4 * v);
-            if (ev && at + 16 <= n_cw) {
-                __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(errpos + at));
+    // LANES lanes at a time: their messages are one contiguous piece of the
+    // stream, staged in LDS and stored in 16-byte vectors by consecutive lanes
+#pragma unroll
+    for (int round = 0; round < 64 / S::LANES; ++round) {
+        if (S::LANES == 64 || lane / S::LANES == uint32_t(round)) {
+            const uint32_t l = lane % S::LANES;
+            if constexpr (K % 4 == 0) {
+#pragma unroll
+                for (int w = 0; w < K; w += 4)
+                    *reinterpret_cast<u32x4*>(buf + l * K + w) = u32x4{out[w], out[w + 1], out[w + 2], out[w + 3]};
             } else {
-                for (int q = 0; q < 16 && at + q < n_cw; ++q) errpos[at + q] = uint8_t(x[q / 4] >> (8 * (q % 4)));
+#pragma unroll
+                for (int w = 0; w < K; ++w) buf[l * K + w] = out[w];
             }
         }
+        wave_sync();
+        const uint64_t dw0 = (wave * 64 + round * S::LANES) * K;
+#pragma unroll
+        for (uint32_t q = 0; q < (S::MSG_DW / 4 + 63) / 64; ++q) {
+            const uint32_t v = lane + 64 * q;
+            if (v >= uint32_t(S::MSG_DW / 4)) break;
+            const uint64_t at = dw0 + 4ull * v;
+            const u32x4 x = *reinterpret_cast<const u32x4*>(buf + 4 * v);
+            if (at + 4 <= data_dwords) {
+                __builtin_nontemporal_store(x, reinterpret_cast<u32x4a8*>(data + at));
+            } else {
+                for (int i = 0; i < 4 && at + i < data_dwords; ++i) data[at + i] = x[i];
+            }
+        }
+        wave_sync();
     }
 }
 
-// Natural layout -> planes: one lane transposes 32 codewords, one storage
-// dword at a time.
-template <int R>
-__global__ __launch_bounds__(256) void to_planes_kernel(const uint32_t* __restrict__ cw, uint64_t n_cw,
-                                                        uint32_t* __restrict__ planes, uint64_t plane_dwords)
+// Natural layout -> planes.  A wave converts 2048 consecutive codewords, 32
+// per lane, one storage dword at a time: the words arrive as 16-byte vectors
+// by consecutive lanes (coalesced), pass through LDS to the lane that owns
+// them, and a lane's 32 dwords are transposed in registers into one dword of
+// each of 32 planes, so every store writes 256 contiguous bytes of a plane.
+// Only the dwords that hold positions are staged (one of two for r <= 5), in
+// an 8 KB buffer per wave that the dwords of a codeword take in turn.
+// 16-byte slots are rotated per block of eight, so a lane's reads (128 bytes
+// apart from its neighbours') spread over the banks.
+//
+// Bound by HBM.  The first form (a lane loading its 32 codewords itself, 4
+// bytes at a 256-byte lane stride) spent its time on the 64 cache lines that
+// each load touched: 82 us (r = 5) and 130 us (r = 6) for 2^24 codewords,
+// against 40 and 47 us now (5.0 and 5.6 TB/s).  Consecutive blocks go to one
+// XCD in slices of 32 (1: 3-8% slower at 2^24 codewords, equal at 2^26).
+//
+// NT: nontemporal plane stores.  They are 4-7% faster when every plane starts
+// on a 128-byte line, so that a wave's 256 bytes are whole lines (r = 6, 2^24
+// codewords: 46.8 against 49.7 us); otherwise two waves share the lines at
+// the ends of their pieces, and plain stores, which the L2 merges, win by 4-16%
+// (r = 7: 115 against 137 us).
+constexpr int kToPlanesWaves = 4;
+constexpr uint32_t kToPlanesXcdChunk = 32;
+constexpr uint32_t kToPlanesCw = 2048;        // codewords per wave
+
+template <int R, bool NT>
+__global__ __launch_bounds__(64 * kToPlanesWaves) void to_planes_kernel(const uint64_t* __restrict__ cw,
+                                                                        uint64_t n_cw,
+                                                                        uint32_t* __restrict__ planes,
+                                                                        uint64_t plane_dwords)
 {
-    constexpr int N = Code<R>::N, DW = Code<R>::DW;
-    const uint64_t g = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    const uint64_t groups = (n_cw + 31) / 32;
-    if (g >= groups) return;
+    constexpr int N = Code<R>::N, WPC = Code<R>::WPC;
+    constexpr int ND = (N + 31) / 32;         // storage dwords that hold positions
+    constexpr int NV = 16 * WPC;              // 16-byte vectors per lane
+    constexpr int PER = 2 / WPC;              // codewords per vector
+    __shared__ u32x4 lds_raw[kToPlanesWaves][kToPlanesCw / 4];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t wave = uint64_t(xcd_block(blockIdx.x, gridDim.x, kToPlanesXcdChunk)) * kToPlanesWaves + wib;
+    if (wave * kToPlanesCw >= n_cw) return;
+    uint32_t* buf = reinterpret_cast<uint32_t*>(&lds_raw[wib][0]);
+
+    uint32_t in[NV][PER][ND];
+    const u32x4a8* src = reinterpret_cast<const u32x4a8*>(cw + wave * kToPlanesCw * WPC) + lane;
+    const uint64_t rem = (n_cw - wave * kToPlanesCw) * WPC;      // input words left
+    const bool full = rem >= uint64_t(kToPlanesCw) * WPC;
 #pragma unroll
-    for (int d = 0; d < DW; ++d) {
-        if (32 * d >= N) break;
+    for (int v = 0; v < NV; ++v) {
+        u32x4 x = {0u, 0u, 0u, 0u};
+        const uint64_t w = 2 * (64u * uint64_t(v) + lane);       // first word of this lane's vector v
+        if (full || w + 1 < rem) {
+            x = __builtin_nontemporal_load(src + 64 * v);
+        } else if (w < rem) {
+            const uint64_t y = reinterpret_cast<const uint64_t*>(src + 64 * v)[0];
+            x.x = uint32_t(y);
+            x.y = uint32_t(y >> 32);
+        }
+#pragma unroll
+        for (int c = 0; c < PER; ++c)
+#pragma unroll
+            for (int d = 0; d < ND; ++d) in[v][c][d] = x[c * 2 * WPC + d];
+    }
+
+    const uint64_t g = wave * 64 + lane;
+    const bool stores = 32 * g < n_cw;
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+        if (d > 0) wave_sync();
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const uint32_t c = (64u * v + lane) * PER;           // first codeword of the vector
+            const uint32_t slot = c / 4;
+            uint32_t* at = buf + 4 * (slot ^ ((slot >> 3) & 7u)) + c % 4;
+            if constexpr (PER == 2)
+                *reinterpret_cast<uint2*>(at) = make_uint2(in[v][0][d], in[v][1][d]);
+            else
+                *at = in[v][0][d];
+        }
+        wave_sync();
         uint32_t A[32];
 #pragma unroll
-        for (int c = 0; c < 32; ++c) {
-            const uint64_t i = 32 * g + c;
-            A[c] = i < n_cw ? cw[i * DW + d] : 0u;
+        for (uint32_t q = 0; q < 8; ++q) {
+            const u32x4 x = *reinterpret_cast<const u32x4*>(buf + 4 * (8 * lane + (q ^ (lane & 7u))));
+            A[4 * q + 0] = x.x;
+            A[4 * q + 1] = x.y;
+            A[4 * q + 2] = x.z;
+            A[4 * q + 3] = x.w;
         }
         transpose32(A);
+        if (stores) {
+            uint32_t* dst = planes + uint64_t(32 * d) * plane_dwords + g;
 #pragma unroll
-        for (int b = 0; b < 32; ++b)
-            if (32 * d + b < N) planes[uint64_t(32 * d + b) * plane_dwords + g] = A[b];
+            for (int b = 0; b < 32; ++b) {
+                if (32 * d + b >= N) break;
+                if constexpr (NT)
+                    __builtin_nontemporal_store(A[b], dst + uint64_t(b) * plane_dwords);
+                else
+                    dst[uint64_t(b) * plane_dwords] = A[b];
+            }
+        }
     }
 }
 
@@ -264,7 +406,10 @@ void launch_planes(const uint64_t* planes, uint64_t plane_words, uint64_t n_cw, 
     const uint64_t waves = ((n_cw + 31) / 32 + 63) / 64;
     const uint64_t blocks = (waves + S::WAVES - 1) / S::WAVES;
     const uint64_t data_dwords = hamming_data_bytes(n_cw, R) / 4;
-    hipLaunchKernelGGL(decode_planes_kernel<R>, dim3(uint32_t(blocks)), dim3(64 * S::WAVES), 0, stream,
+    void (*const kernel)(const uint32_t*, uint64_t, uint64_t, uint32_t*, uint64_t, uint8_t*, uint32_t) =
+        uint64_t(Code<R>::N) * n_cw / 8 > kPlanesCachedBytes ? decode_planes_kernel<R, true>
+                                                             : decode_planes_kernel<R, false>;
+    hipLaunchKernelGGL(kernel, dim3(uint32_t(blocks)), dim3(64 * S::WAVES), 0, stream,
                        reinterpret_cast<const uint32_t*>(planes), plane_words * 2, n_cw,
                        static_cast<uint32_t*>(data), data_dwords, errpos, flags);
 }
@@ -273,9 +418,11 @@ template <int R>
 void launch_to_planes(const uint64_t* cw, uint64_t n_cw, uint64_t* planes, uint64_t plane_words, hipStream_t stream)
 {
     const uint64_t groups = (n_cw + 31) / 32;
-    hipLaunchKernelGGL(to_planes_kernel<R>, dim3(uint32_t((groups + 255) / 256)), dim3(256), 0, stream,
-                       reinterpret_cast<const uint32_t*>(cw), n_cw, reinterpret_cast<uint32_t*>(planes),
-                       plane_words * 2);
+    const bool whole_lines = ((reinterpret_cast<uintptr_t>(planes) | (plane_words * 8)) & 127u) == 0;
+    void (*const kernel)(const uint64_t*, uint64_t, uint32_t*, uint64_t) =
+        whole_lines ? to_planes_kernel<R, true> : to_planes_kernel<R, false>;
+    hipLaunchKernelGGL(kernel, dim3(uint32_t((groups + 255) / 256)), dim3(64 * kToPlanesWaves), 0, stream, cw, n_cw,
+                       reinterpret_cast<uint32_t*>(planes), plane_words * 2);
 }
 
 }  // namespace
@@ -304,7 +451,6 @@ int hamming_decode_planes(const uint64_t* planes, uint64_t plane_words, uint64_t
     if ((reinterpret_cast<uintptr_t>(planes) & 7u) || (reinterpret_cast<uintptr_t>(data_out) & 7u))
         return HAMMING_EALIGN;
     uint32_t flags = 0;
-    if (!(reinterpret_cast<uintptr_t>(data_out) & 15u)) flags |= hm::kFlagOut16;
     if (errpos_out && !(reinterpret_cast<uintptr_t>(errpos_out) & 15u)) flags |= hm::kFlagEpVec;
     switch (r) {
     case 3: hm::launch_planes<3>(planes, plane_words, n_cw, data_out, errpos_out, flags, stream); break;

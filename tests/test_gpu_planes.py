@@ -87,6 +87,34 @@ def test_to_planes_matches_cpu_rearrangement(gpu_device, r, n_cw):
     assert np.array_equal(got, to_planes(y, n_cw, r))
 
 
+@pytest.mark.parametrize("r", [3, 5, 6, 7])
+@pytest.mark.parametrize("n_cw", [2047, 2048, 2049, 8192 + 33, 16384])
+@pytest.mark.parametrize("spare", [0, 1])
+def test_to_planes_tiles_lines_and_canaries(gpu_device, r, n_cw, spare):
+    """Around the converter's 2048-codeword tiles, planes on whole 128-byte
+    lines (spare = 0) and off them, from codewords at an odd word; plane words
+    past the packet keep their contents."""
+    import torch
+
+    y = received_words(synth.workload_seed("gpu-to-planes-tiles", r, n_cw), n_cw, r, p_single=0.3)
+    pw = ((n_cw + 63) // 64 + 15) // 16 * 16 + 16 + spare
+    N = (1 << r) - 1
+    raw = torch.full((N * pw + 16,), 0x5A5A5A5A5A5A5A5A, dtype=torch.int64, device=gpu_device)
+    start = (-(raw.data_ptr() // 8)) % 16 + spare
+    arena = torch.zeros(y.size + 1, dtype=torch.int64, device=gpu_device)
+    arena[1:] = to_device(y, gpu_device)
+    hm.hamming_to_planes(arena[1:], n_cw, r, raw[start:], pw)
+    torch.cuda.synchronize()
+    got = raw.cpu().numpy()
+    body = got[start:start + N * pw].view(np.uint32).reshape(N, 2 * pw)
+    ref = to_planes(y, n_cw, r, pw).view(np.uint32).reshape(N, 2 * pw)
+    dwords = (n_cw + 31) // 32
+    assert np.array_equal(body[:, :dwords], ref[:, :dwords])
+    assert (body[:, dwords:] == 0x5A5A5A5A).all()
+    outside = np.concatenate([got[:start], got[start + N * pw:]])
+    assert (outside == 0x5A5A5A5A5A5A5A5A).all()
+
+
 @pytest.mark.parametrize("r,n_cw", [(3, 1 << 26), (5, 1 << 26), (7, 1 << 25)])
 def test_planes_full_size_equals_plain_decode_and_oracle_samples(gpu_device, r, n_cw):
     """Full-size packets: the plane decode equals the plain decode of the
