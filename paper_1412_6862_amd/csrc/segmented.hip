@@ -4,8 +4,12 @@
 // message segments are merged back into the M-byte packet.  The checksum of a
 // segment is the XOR over its index sets (Sec. III.A, III.C, Algorithm 1).
 //
-// A group of threads per packet (part of a wave, a wave or a workgroup): the
-// 128-position windows of all segments form one flat list dealt to the
+// A group of threads per packet (part of a wave, a wave or a workgroup), in one
+// of two forms.  A wave whose packets have one shape and lie at one stride takes
+// the part form (below, at its kernels); everything else, and the workgroup
+// per packet, takes the window form:
+//
+// The 128-position windows of all segments form one flat list dealt to the
 // threads.  Decoding, a thread reads each of its windows once from HBM (an
 // unaligned three-word span), folds it into its partial syndrome of the
 // segment and ORs the window's message bits (one run of consecutive message
@@ -25,6 +29,7 @@
 #include "hamming.h"
 #include "launch.h"
 #include "seg_bits.h"
+#include "seg_parts.h"
 #include "tile.h"
 
 using hm::funnel128;
@@ -32,6 +37,7 @@ using hm::head_expand;
 using hm::head_message;
 using hm::mask_top;
 using hm::run_start;
+using hm::small_div;
 using hm::u32x4;
 using hm::u32x4a8;
 using hm::wave_sync;
@@ -87,8 +93,8 @@ __device__ __forceinline__ bool make_layout(uint32_t msg_bytes, uint32_t t, uint
     if (t < 1 || t > HAMMING_SEG_MAX_T || msg_bytes < 1 || msg_bytes > max_msg_bytes || 8u * msg_bytes < t) return false;
     const uint32_t bits = 8u * msg_bytes;
     L.t = t;
-    L.q = bits / t;
-    L.rem = bits % t;
+    L.q = small_div(bits, t);                                  // bits <= 2^15
+    L.rem = bits - L.q * t;
     if (L.q + (L.rem ? 1u : 0u) > HAMMING_SEG_MAX_K) return false;
     L.nA = L.q + 1 + seg_checksum_bits(L.q + 1);
     L.nB = L.q + seg_checksum_bits(L.q);
@@ -340,22 +346,24 @@ struct SegArgs {
     uint16_t* syndromes;
     uint64_t syndrome_count;
     uint8_t* status;
-    uint32_t slice_words;      // per-packet LDS buffer (accumulators excluded)
+    uint32_t slice_words;      // per-packet LDS buffer of the window form (accumulators excluded)
+    uint32_t slot_dwords;      // LDS dwords per packet of the part form's kernels
+    uint32_t cached;           // read packets with ordinary (1) or nontemporal (0) loads
 };
 
 // Per-packet accumulators after the buffer: X, one 64-bit word per segment,
 // then H, one 32-bit word per segment.
 constexpr uint32_t kAccWords = HAMMING_SEG_MAX_T + HAMMING_SEG_MAX_T / 2;
 
-// Decode packet pk with GROUP threads (gl = 0..GROUP-1); Mb is the packet's
-// message buffer in LDS (at least mw + 3 words) and acc its accumulators.
-// With GROUP < 64 several packets share a wave, so pk, the descriptor and the
+// Decode packet pk, of descriptor d, with GROUP threads (gl = 0..GROUP-1); Mb
+// is the packet's message buffer in LDS (at least mw + 3 words) and acc its
+// accumulators.  With GROUP < 64 several packets share a wave, so pk, the descriptor and the
 // layout are per-lane values and wave-wide ballots are masked to the group.
 // Every thread of a group takes the same branches at the barriers.
 template <uint32_t GROUP, uint32_t BATCH>
-__device__ __forceinline__ void decode_packet(const SegArgs& a, uint64_t pk, uint32_t gl, uint64_t* Mb, uint64_t* acc)
+__device__ __forceinline__ void decode_packet(const SegArgs& a, const hamming_seg_packet& d, uint64_t pk, uint32_t gl,
+                                              uint64_t* Mb, uint64_t* acc)
 {
-    const hamming_seg_packet d = a.descs[pk];
     const uint32_t M = d.msg_bytes, t = d.t;
     Layout Lo;
     const bool shape_ok = make_layout(M, t, a.max_msg_bytes, Lo);
@@ -423,13 +431,13 @@ __device__ __forceinline__ void decode_packet(const SegArgs& a, uint64_t pk, uin
     if ((mw & 1) && gl == 0) __builtin_nontemporal_store(Mb[mw - 1], dst + mw - 1);
 }
 
-// Encode packet pk with GROUP threads; E is the packet's encoded buffer in
-// LDS (at least ew + 3 words, E[0] in front of the stream) and acc its
+// Encode a packet of descriptor d with GROUP threads; E is the packet's encoded
+// buffer in LDS (at least ew + 3 words, E[0] in front of the stream) and acc its
 // accumulators.  A descriptor this launch cannot take is skipped.
 template <uint32_t GROUP, uint32_t BATCH>
-__device__ __forceinline__ void encode_packet(const SegArgs& a, uint64_t pk, uint32_t gl, uint64_t* E, uint64_t* acc)
+__device__ __forceinline__ void encode_packet(const SegArgs& a, const hamming_seg_packet& d, uint32_t gl, uint64_t* E,
+                                              uint64_t* acc)
 {
-    const hamming_seg_packet d = a.descs[pk];
     const uint32_t M = d.msg_bytes, t = d.t;
     Layout Lo;
     const bool shape_ok = make_layout(M, t, a.max_msg_bytes, Lo);
@@ -475,28 +483,417 @@ __device__ __forceinline__ void encode_packet(const SegArgs& a, uint64_t pk, uin
     if ((ew & 1) && gl == 0) __builtin_nontemporal_store(E[ew], dst + ew - 1);
 }
 
-// 256 / GROUP packets per block, GROUP threads each: part of a wave, a wave,
-// or (GROUP = 256) the whole block on one packet, the latency form.
+// ---- part form ---------------------------------------------------------------
+//
+// The packets of a wave that have one shape and lie at one stride in either
+// arena (a batch of equal packets, end to end or with a gap after each) take
+// this form: their words are one run, which the 64 lanes copy into LDS and the
+// results out of it in whole cache lines.  The bits are then dealt by segment: every lane owns one part
+// of one segment (seg_parts.h), reads it from LDS into registers, folds its
+// syndrome there and ORs its message (or encoded) bits into place over the run
+// it came from.
+//
+// What bounded the window form was neither its instructions nor its latency
+// but how its loads met the memory: a group's loads start wherever its packet
+// does and cover 128 or 256 bytes, so most cache lines were asked for twice.
+// A copy of the kernel with all bit work taken out ran no faster (1200-byte
+// packets, t = 4, 2^19 of them: 253-285 us, decoding 256-281 us); moving the
+// same words as one run per wave, with the bit work, takes 200 us (6.4 TB/s).
+// Encoding 2^18 packets of 800 bytes, t = 5: 104 -> 75 us (5.7 TB/s).
+
+typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+constexpr uint32_t kPartLoads = 8;          // 16-byte loads a lane has in flight while a run is staged
+constexpr uint32_t kPartPad = 4;            // dwords in front of the run in LDS
+
+// LDS dwords of a wave beside its run: the pad, the run's shift within a line,
+// what is cleared and ORed in after it, and one syndrome per lane.  Lanes past
+// their segment's last window read up to 43 + 4 NW dwords past the run's start
+// and words, which the syndromes cover.
+constexpr uint32_t kPartRunExtra = kPartPad + 30u + 8u + 64u;
+constexpr uint32_t kPartStores = 4;         // 16-byte vectors it reads back before it stores the first
+
+// A run of consecutive 64-bit words that a wave moves between global memory
+// and LDS in 16-byte vectors, lane 0 starting on a 128-byte line: word w of
+// the run sits at LDS dword kPartPad + 2 (shift + w), vector j holds words
+// 2j - shift and 2j + 1 - shift, and vectors lo .. hi - 1 lie in the run
+// altogether.  The first and the last word may lie in no whole vector; they
+// are moved alone, so no access leaves the run.
+struct Run {
+    uint32_t words, shift, lo, hi;
+
+    __device__ Run(const void* first_word, uint32_t words_)
+        : words(words_), shift(uint32_t(reinterpret_cast<uintptr_t>(first_word) >> 3) & 15u),
+          lo((shift + 1u) / 2u), hi((shift + words) / 2u) {}
+
+    // LDS dword of word w.
+    __device__ uint32_t at(uint32_t w) const { return kPartPad + 2u * (shift + w); }
+
+    template <bool NT>
+    __device__ __forceinline__ void load(const uint64_t* src, uint32_t* S, uint32_t lane) const
+    {
+        const char* from = reinterpret_cast<const char*>(src - shift);     // uniform: loads take a 32-bit offset
+        const uint32_t edge = lane == 0 ? 0u : words - 1u;
+        uint64_t edge_word = 0;
+        if (lane < 2) edge_word = src[edge];
+        for (uint32_t base = 0; base < hi && lo < hi; base += kPartLoads * 64) {
+            u32x4 x[kPartLoads];
+            uint32_t j[kPartLoads];
+            // lanes outside the run move its first or last whole vector once
+            // more: a load under a branch of its own would wait for the others
+#pragma unroll
+            for (uint32_t u = 0; u < kPartLoads; ++u) {
+                if (base + u * 64 >= hi) continue;
+                j[u] = min(max(base + u * 64 + lane, lo), hi - 1u);
+                const u32x4a8* v = reinterpret_cast<const u32x4a8*>(from + 16u * j[u]);
+                x[u] = NT ? __builtin_nontemporal_load(v) : *v;
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kPartLoads; ++u)
+                if (base + u * 64 < hi) *reinterpret_cast<u32x4*>(S + kPartPad + 4u * j[u]) = x[u];
+        }
+        if (lane < 2)
+            *reinterpret_cast<uint2*>(S + at(edge)) = make_uint2(uint32_t(edge_word), uint32_t(edge_word >> 32));
+    }
+
+    // Clears the run's dwords in LDS and at least `more` dwords after them.
+    __device__ __forceinline__ void clear(uint32_t more, uint32_t* S, uint32_t lane) const
+    {
+        for (uint32_t j = lane; 4u * j < 2u * (shift + words) + more; j += 64)
+            *reinterpret_cast<u32x4*>(S + kPartPad + 4u * j) = u32x4{0u, 0u, 0u, 0u};
+    }
+
+    // Stores the run.  Of every `stride` words of it `packet` are a packet's and
+    // the rest the gap after it, which is left as it was.
+    __device__ __forceinline__ void store(uint64_t* dst, const uint32_t* S, uint32_t lane, uint32_t packet,
+                                          uint32_t stride) const
+    {
+        if (packet != stride) {
+            for (uint32_t j = lane; j < (shift + words + 1u) / 2u; j += 64) {
+                const u32x4 x = *reinterpret_cast<const u32x4*>(S + kPartPad + 4u * j);
+                const int32_t w = int32_t(2u * j) - int32_t(shift);                  // the vector's first word
+                const uint32_t in0 = w < 0 ? packet : uint32_t(w) - small_div(uint32_t(w), stride) * stride;
+                const uint32_t in1 = w + 1 < 0 ? packet : w < 0 || in0 + 1u == stride ? 0u : in0 + 1u;
+                const bool has0 = in0 < packet, has1 = in1 < packet && uint32_t(w + 1) < words;
+                if (has0 && has1)
+                    __builtin_nontemporal_store(x, reinterpret_cast<u32x4a8*>(dst + w));
+                else if (has0)
+                    __builtin_nontemporal_store(uint64_t(x.x) | (uint64_t(x.y) << 32), dst + w);
+                else if (has1)
+                    __builtin_nontemporal_store(uint64_t(x.z) | (uint64_t(x.w) << 32), dst + w + 1);
+            }
+            return;
+        }
+        char* to = reinterpret_cast<char*>(dst - shift);
+        for (uint32_t base = 0; base < hi; base += kPartStores * 64) {
+            u32x4 x[kPartStores];
+#pragma unroll
+            for (uint32_t u = 0; u < kPartStores; ++u) {
+                if (base + u * 64 >= hi) continue;
+                x[u] = *reinterpret_cast<const u32x4*>(S + kPartPad + 4u * min(base + u * 64 + lane, hi - 1u));
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < kPartStores; ++u) {
+                const uint32_t j = base + u * 64 + lane;
+                if (j >= lo && j < hi) __builtin_nontemporal_store(x[u], reinterpret_cast<u32x4a8*>(to + 16u * j));
+            }
+        }
+        if (lane < 2 && ((lane == 0 ? shift : shift + words) & 1u)) {
+            const uint32_t w = lane == 0 ? 0u : words - 1u;
+            const uint2 y = *reinterpret_cast<const uint2*>(S + at(w));
+            __builtin_nontemporal_store(uint64_t(y.x) | (uint64_t(y.y) << 32), dst + w);
+        }
+    }
+};
+
+__device__ __forceinline__ uint64_t readfirstlane64(uint64_t v)
+{
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v));
+    return lo | (uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(v >> 32))) << 32);
+}
+
+// A lane's part: windows v0 .. v0 + cnt - 1 of segment i (none when cnt = 0).
+struct Part {
+    uint32_t i, v0, cnt, K, o;
+    int32_t n;
+
+    __device__ Part(const Layout& Lo, const hm::Parts& P, uint32_t gl)
+    {
+        const uint32_t seg = P.segment(gl);
+        const bool mine = seg < Lo.t;
+        i = mine ? seg : 0u;
+        v0 = (gl - seg * P.parts) * P.len;
+        K = Lo.K(i);
+        o = Lo.o(i);
+        n = mine ? int32_t(Lo.n(i)) : -1;
+        const uint32_t nv = mine ? (i < Lo.rem ? Lo.vA : Lo.vB) : 0u;
+        v0 = min(v0, nv);
+        cnt = min(nv - v0, P.len);
+    }
+};
+
+// Window of five dwords at LDS dword p, bit sh (0..31): four dwords.
+__device__ __forceinline__ void read_window(const uint32_t* p, uint32_t sh, uint32_t (&x)[4])
+{
+    const u32x4 w = *reinterpret_cast<const u32x4a4*>(p);
+    const uint32_t e = p[4];
+    x[0] = hm::align32(w.y, w.x, sh);
+    x[1] = hm::align32(w.z, w.y, sh);
+    x[2] = hm::align32(w.w, w.z, sh);
+    x[3] = hm::align32(e, w.w, sh);
+}
+
+__device__ __forceinline__ void or_window(uint32_t* p, const hm::Placed& w)
+{
+#pragma unroll
+    for (int k = 0; k < 5; ++k) atomicOr(p + w.first + k, w.y[k]);
+}
+
+// The packets of a wave: their layout and parts, encoded and message words,
+// the words from one packet to the next (es, ms) and the first words of their
+// runs.  W is the wave's LDS and X (within it) one syndrome per lane.
+struct WaveRun {
+    Layout Lo;
+    hm::Parts P;
+    uint32_t ew, mw, es, ms;
+    uint64_t *enc, *msg;
+    uint32_t *W, *X;
+};
+
+// Decodes the wave's packets with GROUP lanes each, every lane its part.  The
+// messages are built over the received words once every lane holds its
+// windows in registers.
+template <uint32_t GROUP, uint32_t NW>
+__device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r, uint64_t pk, uint64_t seg_off)
+{
+    const uint32_t lane = threadIdx.x & 63u, gl = lane % GROUP, slot = lane / GROUP;
+    const Layout& Lo = r.Lo;
+    const hm::Parts& P = r.P;
+    uint32_t* S = r.W;
+    uint32_t* X = r.X + slot * GROUP;
+    const Run in(r.enc, (64 / GROUP - 1) * r.es + r.ew), out(r.msg, (64 / GROUP - 1) * r.ms + r.mw);
+    const uint32_t mb = out.at(slot * r.ms);
+    X[gl] = 0;
+    if (a.cached)
+        in.load<false>(r.enc, S, lane);
+    else
+        in.load<true>(r.enc, S, lane);
+    wave_sync();
+
+    const Part pt(Lo, P, gl);
+    const uint32_t bit = pt.o + 128u * pt.v0 + 32u * in.at(slot * r.es) - 1u;   // LDS bit of position 128 v0
+    const uint32_t* src = S + (bit >> 5);
+    hm::PartSyndrome syn;
+    uint32_t x[NW][4];
+#pragma unroll
+    for (uint32_t u = 0; u < NW; ++u) {
+        if (u < P.len) {
+            read_window(src + 4u * u, bit, x[u]);
+            const int32_t top = pt.n - int32_t(128u * (pt.v0 + u));     // last position of the segment
+            if (top < 127) hm::mask_window(x[u], top);
+            if (u == 0) x[0][0] &= pt.v0 == 0 ? ~1u : ~0u;              // there is no position 0
+            syn.add(x[u], pt.v0 + u);
+        }
+    }
+    const uint32_t sv = syn.value();
+    if (sv) atomicXor(&X[pt.i], sv);
+    wave_sync();
+    out.clear(5u, S, lane);
+    wave_sync();
+#pragma unroll
+    for (uint32_t u = 0; u < NW; ++u) {
+        if (u < pt.cnt) {
+            const uint32_t v = pt.v0 + u;
+            uint32_t at = pt.K + hm::run_base(v);
+            if (u == 0 && v == 0) {
+                hm::compact_head(x[0]);
+                at = pt.K;
+            } else {
+                x[u][0] &= ~hm::is_pow2_window(v);
+            }
+            or_window(S + mb, hm::place_window(x[u], at));
+        }
+    }
+    wave_sync();
+
+    // checksum owners: lane gl has segment gl; an error at a message position
+    // flips that message bit, one at a checksum position changes none
+    uint32_t st = 0;
+    if (gl < Lo.t) {
+        const uint32_t s = X[gl], n = Lo.n(gl);
+        if (s >= 1 && s <= n) {
+            if (s & (s - 1u)) {
+                const uint32_t b = Lo.K(gl) + s - (31u - __clz(s)) - 2u;
+                atomicXor(&S[mb + (b >> 5)], 1u << (b & 31u));
+            }
+            st = 1;
+        } else if (s > n) {
+            st = 2;
+        }
+        if (a.syndromes) a.syndromes[seg_off + gl] = uint16_t(s);
+    }
+    uint64_t mask = ~uint64_t(0);
+    if constexpr (GROUP < 64) mask = ((uint64_t(1) << GROUP) - 1) << (slot * GROUP);
+    const uint64_t any2 = __ballot(st == 2) & mask, any1 = __ballot(st == 1) & mask;
+    if (a.status && gl == 0) a.status[pk] = any2 ? 2 : (any1 ? 1 : 0);
+    wave_sync();
+    out.store(r.msg, S, lane, r.mw, r.ms);
+}
+
+// Encodes the wave's packets: the same parts, each window built from its run
+// of message bits and placed into the encoded packet.
+template <uint32_t GROUP, uint32_t NW>
+__device__ __forceinline__ void encode_parts(const SegArgs& a, const WaveRun& r)
+{
+    const uint32_t lane = threadIdx.x & 63u, gl = lane % GROUP, slot = lane / GROUP;
+    const Layout& Lo = r.Lo;
+    const hm::Parts& P = r.P;
+    uint32_t* S = r.W;
+    uint32_t* X = r.X + slot * GROUP;
+    const Run in(r.msg, (64 / GROUP - 1) * r.ms + r.mw), out(r.enc, (64 / GROUP - 1) * r.es + r.ew);
+    const uint32_t mb = in.at(slot * r.ms), eb = out.at(slot * r.es);
+    X[gl] = 0;
+    if (a.cached)
+        in.load<false>(r.msg, S, lane);
+    else
+        in.load<true>(r.msg, S, lane);
+    wave_sync();
+
+    const Part pt(Lo, P, gl);
+    hm::PartSyndrome syn;
+    uint32_t x[NW][4];
+#pragma unroll
+    for (uint32_t u = 0; u < NW; ++u) {
+        if (u < pt.cnt) {
+            const uint32_t v = pt.v0 + u;
+            const bool head = u == 0 && v == 0;
+            const uint32_t at = pt.K + (head ? 0u : hm::run_base(v));
+            read_window(S + mb + (at >> 5), at, x[u]);
+            if (head)
+                hm::expand_head(x[u]);
+            else
+                x[u][0] &= ~hm::is_pow2_window(v);
+            const int32_t top = pt.n - int32_t(128u * v);
+            if (top < 127) hm::mask_window(x[u], top);
+            syn.add(x[u], v);
+        }
+    }
+    const uint32_t sv = syn.value();
+    if (sv) atomicXor(&X[pt.i], sv);
+    wave_sync();
+    out.clear(6u, S, lane);
+    wave_sync();
+#pragma unroll
+    for (uint32_t u = 0; u < NW; ++u) {
+        // one dword further on, so that the stream bit is never negative
+        if (u < pt.cnt) or_window(S + eb - 1, hm::place_window(x[u], pt.o + 128u * (pt.v0 + u) + 31u));
+    }
+    wave_sync();
+
+    // checksum position 2^j of segment gl takes bit j of the syndrome of its
+    // message bits, which makes the segment's syndrome 0
+    if (gl < Lo.t) {
+        const uint32_t s = X[gl], o = Lo.o(gl);
+        const uint32_t w = (s & 3u) | ((s & 4u) << 1) | ((s & 8u) << 4) | ((s & 16u) << 11) | ((s & 32u) << 26);
+        atomicOr(&S[eb + (o >> 5)], w << (o & 31u));
+        atomicOr(&S[eb + (o >> 5) + 1u], (w >> 1) >> (31u - (o & 31u)));
+        for (uint32_t j = 6; (s >> j) != 0; ++j) {
+            const uint32_t b = o + (1u << j) - 1u;
+            if ((s >> j) & 1u) atomicOr(&S[eb + (b >> 5)], 1u << (b & 31u));
+        }
+    }
+    wave_sync();
+    out.store(r.enc, S, lane, r.ew, r.es);
+}
+
+// Consecutive blocks that each XCD takes in turn (xcd_block): the lines that two
+// blocks share then meet in one L2.  2000-byte packets 353 against 362 us
+// without, 400 to 1200 bytes within 1-3% either way.
+constexpr uint32_t kSegXcdChunk = 8;
+
+// Shortest message of the part form, whose fixed work outweighs its loads below:
+// 128-byte packets 30.2 against 28.6 us in the window form, 250-byte ones 33
+// against 48.
+constexpr uint32_t kPartMinBytes = 192;
+
+// 256 / GROUP packets per block, GROUP <= 64 lanes each.  A wave takes the part
+// form when all its packets are there, have one shape of at least kPartMinBytes
+// whose parts fit NW windows, and lie at one stride in either arena, their runs inside the arenas
+// and inside the wave's LDS; the window form otherwise.
+template <uint32_t GROUP, uint32_t NW, uint32_t BATCH, bool DECODE>
+__global__ __launch_bounds__(64 * kSegWaves) void seg_parts_kernel(SegArgs a)
+{
+    constexpr uint32_t PACKETS = 64 / GROUP;                     // of a wave
+    extern __shared__ uint64_t lds[];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64u);
+    const uint32_t lane = threadIdx.x & 63u, gl = lane % GROUP, slot = lane / GROUP;
+    const uint64_t pk = (uint64_t(hm::xcd_block(blockIdx.x, gridDim.x, kSegXcdChunk)) * kSegWaves + wave) * PACKETS + slot;
+    if (pk >= a.n_packets) return;
+    WaveRun r;
+    const uint32_t wave_dwords = PACKETS * a.slot_dwords;
+    r.W = reinterpret_cast<uint32_t*>(lds) + wave * wave_dwords;
+    r.X = r.W + wave_dwords - 64u;
+    const hamming_seg_packet d = a.descs[pk];
+    const uint32_t M = __builtin_amdgcn_readfirstlane(d.msg_bytes), t = __builtin_amdgcn_readfirstlane(d.t);
+    // all 64 lanes are there, and their packets have one shape
+    const bool one_shape = __ballot(d.msg_bytes == M && d.t == t) == ~uint64_t(0);
+    if (one_shape && t <= GROUP && (GROUP == 64 || M >= kPartMinBytes) && make_layout(M, t, a.max_msg_bytes, r.Lo)) {
+        const uint64_t e0 = readfirstlane64(d.enc_word_off), m0 = readfirstlane64(d.msg_word_off);
+        r.P = hm::make_parts(t, r.Lo.rem ? r.Lo.vA : r.Lo.vB, GROUP);
+        r.ew = (r.Lo.total + 63u) / 64u;
+        r.mw = (M + 7u) / 8u;
+        r.es = r.ew;
+        r.ms = r.mw;
+        if constexpr (PACKETS > 1) {
+            r.es = __builtin_amdgcn_readlane(uint32_t(d.enc_word_off - e0), GROUP);        // packet 1's distance
+            r.ms = __builtin_amdgcn_readlane(uint32_t(d.msg_word_off - m0), GROUP);
+        }
+        bool alike = d.enc_word_off == e0 + uint64_t(slot) * r.es && d.msg_word_off == m0 + uint64_t(slot) * r.ms;
+        if constexpr (DECODE)
+            alike = alike && (!a.syndromes || (d.seg_off <= a.syndrome_count && t <= a.syndrome_count - d.seg_off));
+        const uint32_t most = (wave_dwords - kPartRunExtra) / 2u;                      // words of a run in LDS
+        const bool apart = r.es >= r.ew && r.ms >= r.mw && r.es <= most && r.ms <= most;
+        const uint32_t eruns = (PACKETS - 1) * r.es + r.ew, mruns = (PACKETS - 1) * r.ms + r.mw;
+        if (r.P.len <= NW && apart && eruns <= most && mruns <= most && e0 <= a.enc_words &&
+            eruns <= a.enc_words - e0 && m0 <= a.msg_words && mruns <= a.msg_words - m0 &&
+            __ballot(alike) == ~uint64_t(0)) {
+            r.enc = const_cast<uint64_t*>(a.enc) + e0;
+            r.msg = a.msg + m0;
+            if constexpr (DECODE)
+                decode_parts<GROUP, NW>(a, r, pk, d.seg_off);
+            else
+                encode_parts<GROUP, NW>(a, r);
+            return;
+        }
+    }
+    if constexpr (GROUP == 64) {
+        // one packet of any valid shape fits its wave, so this one is not valid
+        if constexpr (DECODE)
+            if (a.status && gl == 0) a.status[pk] = HAMMING_SEG_INVALID;
+    } else {
+        uint64_t* slice = reinterpret_cast<uint64_t*>(r.W + slot * a.slot_dwords);
+        if constexpr (DECODE)
+            decode_packet<GROUP, BATCH>(a, d, pk, gl, slice, slice + a.slice_words);
+        else
+            encode_packet<GROUP, BATCH>(a, d, gl, slice, slice + a.slice_words);
+    }
+}
+
+// A workgroup per packet, the latency form.
 template <uint32_t GROUP, uint32_t BATCH>
 __global__ __launch_bounds__(64 * kSegWaves) void seg_decode_kernel(SegArgs a)
 {
     extern __shared__ uint64_t lds[];
-    const uint32_t slot = threadIdx.x / GROUP;
-    const uint64_t pk = uint64_t(blockIdx.x) * (64 * kSegWaves / GROUP) + slot;
-    if (pk >= a.n_packets) return;
-    uint64_t* slice = lds + slot * (a.slice_words + kAccWords);
-    decode_packet<GROUP, BATCH>(a, pk, threadIdx.x % GROUP, slice, slice + a.slice_words);
+    const uint64_t pk = blockIdx.x;
+    decode_packet<GROUP, BATCH>(a, a.descs[pk], pk, threadIdx.x, lds, lds + a.slice_words);
 }
 
 template <uint32_t GROUP, uint32_t BATCH>
 __global__ __launch_bounds__(64 * kSegWaves) void seg_encode_kernel(SegArgs a)
 {
     extern __shared__ uint64_t lds[];
-    const uint32_t slot = threadIdx.x / GROUP;
-    const uint64_t pk = uint64_t(blockIdx.x) * (64 * kSegWaves / GROUP) + slot;
-    if (pk >= a.n_packets) return;
-    uint64_t* slice = lds + slot * (a.slice_words + kAccWords);
-    encode_packet<GROUP, BATCH>(a, pk, threadIdx.x % GROUP, slice, slice + a.slice_words);
+    const uint64_t pk = blockIdx.x;
+    encode_packet<GROUP, BATCH>(a, a.descs[pk], threadIdx.x, lds, lds + a.slice_words);
 }
 
 // Threads per packet when the caller leaves the choice to the library: a
@@ -508,46 +905,78 @@ std::atomic<uint32_t> g_seg_threads{0};
 uint32_t auto_threads_per_packet(uint32_t n_packets, uint32_t max_msg_bytes, bool decode)
 {
     if (n_packets <= kWideMaxPackets) return 256;
-    // measured on the Table 1 grid (400..2000-byte packets) and between its
-    // sizes: 8 threads per packet are fastest at 400 bytes (the per-packet
-    // overhead is shared by eight packets of a wave) and, decoding, at 640
-    // and 800 bytes for every t; 16 beat 8, 32 and 64 from 1000 bytes on
-    if (max_msg_bytes <= (decode ? 896u : 640u)) return 8u;
+    // 8 lanes share the per-packet work between eight packets of a wave, 16
+    // have fewer windows each.  2^19 equal packets, 8 against 16: decode 500
+    // bytes 105-113 against 119 us, 640 bytes 130-134 against 121-124; encode
+    // 640 bytes 127 against 141 us, 800 bytes 176-180 against 158-161.  From
+    // there 16 win up to 2000 bytes (339 us, 32: 344) for every t
+    if (max_msg_bytes <= (decode ? 640u : 704u)) return 8u;
     return max_msg_bytes <= 2048 ? 16u : (max_msg_bytes <= 3072 ? 32u : 64u);
 }
 
-template <uint32_t GROUP, uint32_t BATCH, bool DECODE>
-constexpr void (*seg_kernel())(SegArgs)
+// LDS dwords per packet of the part form's kernels (a wave has 64 / group): the
+// encoded words (at most 16 checksum bits for each of t <= group segments) and
+// the wave's share of kPartRunExtra; at least what the window form takes.
+uint32_t part_slot_dwords(uint32_t max_msg_bytes, uint32_t group, uint32_t slice_words)
 {
-    if constexpr (DECODE)
-        return seg_decode_kernel<GROUP, BATCH>;
-    else
-        return seg_encode_kernel<GROUP, BATCH>;
+    const uint32_t ew = (8u * max_msg_bytes + 16u * (group < HAMMING_SEG_MAX_T ? group : HAMMING_SEG_MAX_T) + 63u) / 64u;
+    const uint32_t packets = 64u / group;
+    const uint32_t parts = 2u * ew + (kPartRunExtra + packets - 1u) / packets;
+    const uint32_t windows = group < 64 ? 2u * (slice_words + kAccWords) : 0u;
+    return ((parts > windows ? parts : windows) + 3u) & ~3u;
 }
 
-// Launches the decode or encode of n_packets with the configured (or
-// automatic) group size.  Windows a thread loads ahead: 2 while a thread has
-// at most about five windows (the unused slots of a last batch cost loads and
-// walk steps), 4 above (more loads in flight); measured on the Table 1 grid.
-template <bool DECODE>
-void launch(const SegArgs& a, uint32_t n_packets, uint32_t max_msg_bytes, hipStream_t stream)
+// The kernel for GROUP lanes per packet, with registers for 8 (encoding 9: the
+// compiler then needs 65 registers, with 8 it takes 86) or 12 windows in a lane.  A lane's share is max_msg_bytes / (16 group) windows if all
+// lanes have one; the largest share of t <= 8 segments is about 1.5 times that.
+// The window form loads 2 windows ahead while a thread has about five of them
+// (unused slots of a last batch cost loads and walk steps), 4 above (more
+// loads in flight); measured on the Table 1 grid.
+template <uint32_t GROUP, bool DECODE>
+void (*part_kernel(uint32_t max_msg_bytes))(SegArgs)
 {
+    if constexpr (GROUP == 64) {
+        return seg_parts_kernel<64, 6, 2, DECODE>;       // six are enough for every shape
+    } else {
+        const bool wide = max_msg_bytes > 80u * GROUP;
+        return wide ? seg_parts_kernel<GROUP, 12, 4, DECODE> : seg_parts_kernel<GROUP, DECODE ? 8 : 9, 2, DECODE>;
+    }
+}
+
+// Batches of at most this many message bytes are read with ordinary loads,
+// larger ones with nontemporal loads.  Packets are usually decoded soon after
+// they were written, and half the 256 MB Infinity Cache can still hold them:
+// 2^16 packets of 1200 bytes 28 against 31 us, of 2000 bytes 43 against 48 us.
+// 2^19 packets, which it cannot hold, take 2-3% longer that way (1200 bytes
+// 224 against 219 us, 2000 bytes 345 against 339 us).
+constexpr uint64_t kSegCachedBytes = uint64_t(128) << 20;
+
+// Launches the decode or encode of n_packets with the configured (or
+// automatic) group size.
+template <bool DECODE>
+void launch(const SegArgs& a0, uint32_t n_packets, uint32_t max_msg_bytes, hipStream_t stream)
+{
+    SegArgs a = a0;
+    a.cached = uint64_t(n_packets) * max_msg_bytes <= kSegCachedBytes ? 1u : 0u;
     uint32_t group = g_seg_threads.load();
     if (group == 0) group = auto_threads_per_packet(n_packets, max_msg_bytes, DECODE);
-    const bool deep = (8u * max_msg_bytes) / (128u * group) > 5u;
-    void (*kernel)(SegArgs);
-    if (group == 8)
-        kernel = deep ? seg_kernel<8, 4, DECODE>() : seg_kernel<8, 2, DECODE>();
-    else if (group == 16)
-        kernel = deep ? seg_kernel<16, 4, DECODE>() : seg_kernel<16, 2, DECODE>();
-    else if (group == 32)
-        kernel = deep ? seg_kernel<32, 4, DECODE>() : seg_kernel<32, 2, DECODE>();
-    else if (group == 64)   // at most four windows each (HAMMING_SEG_MAX_BYTES)
-        kernel = seg_kernel<64, 2, DECODE>();
-    else
-        kernel = seg_kernel<256, 2, DECODE>();
     const uint32_t per_block = 64 * kSegWaves / group;
-    const size_t lds = size_t(per_block) * (a.slice_words + kAccWords) * 8;
+    void (*kernel)(SegArgs);
+    size_t lds;
+    if (group == 256) {
+        if constexpr (DECODE)
+            kernel = seg_decode_kernel<256, 2>;
+        else
+            kernel = seg_encode_kernel<256, 2>;
+        lds = size_t(a.slice_words + kAccWords) * 8;
+    } else {
+        kernel = group == 8    ? part_kernel<8, DECODE>(max_msg_bytes)
+                 : group == 16 ? part_kernel<16, DECODE>(max_msg_bytes)
+                 : group == 32 ? part_kernel<32, DECODE>(max_msg_bytes)
+                               : part_kernel<64, DECODE>(max_msg_bytes);
+        a.slot_dwords = part_slot_dwords(max_msg_bytes, group, a.slice_words);
+        lds = size_t(per_block) * a.slot_dwords * 4;
+    }
     // one launch per slice of packets that fits a dispatch's 32-bit work-item
     // count; a slice addresses its packets through offset descriptor and
     // status pointers (syndromes are placed by each descriptor's seg_off)
@@ -619,7 +1048,7 @@ int hamming_decode_segmented(const uint64_t* enc_arena, uint64_t enc_words, cons
     if (rc != HAMMING_OK || n_packets == 0) return rc;
     if (syndromes && (reinterpret_cast<uintptr_t>(syndromes) & 1u)) return HAMMING_EALIGN;
     SegArgs a{enc_arena, enc_words, descs, n_packets, max_msg_bytes, msg_arena, msg_words,
-              syndromes, syndromes ? syndrome_count : 0, status, msg_slice_words(max_msg_bytes)};
+              syndromes, syndromes ? syndrome_count : 0, status, msg_slice_words(max_msg_bytes), 0, 0};
     launch<true>(a, n_packets, max_msg_bytes, stream);
     return hipGetLastError() == hipSuccess ? HAMMING_OK : HAMMING_EDEVICE;
 }
@@ -631,7 +1060,7 @@ int hamming_encode_segmented(const uint64_t* msg_arena, uint64_t msg_words, cons
     int rc = check_common(enc_arena, descs, n_packets, msg_arena, max_msg_bytes);
     if (rc != HAMMING_OK || n_packets == 0) return rc;
     SegArgs a{enc_arena, enc_words, descs, n_packets, max_msg_bytes, const_cast<uint64_t*>(msg_arena), msg_words,
-              nullptr, 0, nullptr, enc_slice_words(max_msg_bytes)};
+              nullptr, 0, nullptr, enc_slice_words(max_msg_bytes), 0, 0};
     launch<false>(a, n_packets, max_msg_bytes, stream);
     return hipGetLastError() == hipSuccess ? HAMMING_OK : HAMMING_EDEVICE;
 }

@@ -394,3 +394,55 @@ def test_segmented_full_size_sampled(gpu_device, P, mb, t):
     # single-flip packets decode to what was sent
     one = (st_ref == 1) & ((b2[sample] < 0).all(axis=1))
     assert one.any() and np.array_equal(msg[one, :mb], sent[one])
+
+
+@pytest.mark.parametrize("seg_mode", [8, 16, 32, 64], indirect=True)
+@pytest.mark.parametrize("msg_bytes,t", [(191, 2), (192, 2), (400, 8), (641, 5), (1280, 3), (1281, 7), (2000, 16),
+                                         (4096, 13)])
+@pytest.mark.parametrize("gap", [0, 1, 6, 4000])
+def test_segmented_equal_packets_at_a_stride(gpu_device, seg_mode, msg_bytes, t, gap):
+    """Equal packets end to end, with a gap after each (in either arena) and
+    too far apart for one run, from an odd first word; a last wave with fewer
+    packets.  Both directions against the oracle; gaps are left as they were."""
+    import torch
+
+    P = 70
+    bits = oracle.seg_layout(msg_bytes, t)[3]
+    ew, mw = (bits + 63) // 64, (msg_bytes + 7) // 8
+    es, ms = ew + gap, mw + (gap + 1) // 2
+    seed = synth.workload_seed("gpu-seg-stride", msg_bytes, t)
+    enc = _received(seed, P, msg_bytes, t, 8 * ew, 0.4, 0.2)
+    msgs = synth.packet_bytes(seed, P, msg_bytes)
+    d = np.zeros(P, dtype=hm.seg_packet_dtype())
+    q = np.arange(P, dtype=np.uint64)
+    d["enc_word_off"], d["msg_word_off"], d["seg_off"] = 3 + q * np.uint64(es), 1 + q * np.uint64(ms), q * np.uint64(t)
+    d["msg_bytes"], d["t"] = msg_bytes, t
+    desc = torch.from_numpy(d.view(np.uint8)).to(gpu_device)
+
+    def arena(rows, words, stride, first):
+        a = np.full(first + (P - 1) * stride + words, 0x3C3C3C3C3C3C3C3C, dtype=np.uint64)
+        if rows is not None:
+            full = np.zeros((P, 8 * words), dtype=np.uint8)
+            full[:, :rows.shape[1]] = rows
+            for p in range(P):
+                a[first + p * stride:first + p * stride + words] = full[p].view(np.uint64)
+        return a
+
+    def on_device(a):
+        return torch.from_numpy(a.view(np.int64)).to(gpu_device)
+
+    msg_t, enc_t = on_device(arena(None, mw, ms, 1)), on_device(arena(enc, ew, es, 3))
+    syn = torch.zeros(P * t, dtype=torch.int16, device=gpu_device)
+    st = torch.zeros(P, dtype=torch.uint8, device=gpu_device)
+    hm.hamming_decode_segmented(enc_t, enc_t.numel(), desc, P, msg_bytes, msg_t, msg_t.numel(), syn, syn.numel(), st)
+    torch.cuda.synchronize()
+    m_ref, s_ref, st_ref = oracle.seg_decode_many(enc, msg_bytes, t)
+    assert np.array_equal(msg_t.cpu().numpy().view(np.uint64), arena(m_ref, mw, ms, 1))
+    assert np.array_equal(syn.cpu().numpy().view(np.uint16).reshape(P, t), s_ref)
+    assert np.array_equal(st.cpu().numpy(), st_ref)
+
+    msg_t, enc_t = on_device(arena(msgs, mw, ms, 1)), on_device(arena(None, ew, es, 3))
+    hm.hamming_encode_segmented(msg_t, msg_t.numel(), desc, P, msg_bytes, enc_t, enc_t.numel())
+    torch.cuda.synchronize()
+    want = oracle.seg_encode_many(msgs, t, row_bytes=8 * ew)
+    assert np.array_equal(enc_t.cpu().numpy().view(np.uint64), arena(want, ew, es, 3))
