@@ -187,13 +187,14 @@ uint64_t hamming_batch_workspace_min_bytes(uint32_t max_packets);
  * Batched decode: decode every packet of a device-resident descriptor array.
  * A planning kernel validates each descriptor, writes its status and computes
  * a prefix sum of tiles (64-codeword multiples aligned to each packet's
- * start); two more kernels build tile-to-packet maps; the decode kernel then
- * gives one tile to each wave in global tile order, so packets of any size and
- * r share the GPU as one stream of work.  On a non-NULL stream that is not
- * already capturing, the four kernels are captured once into a hipGraph
+ * start); a second kernel maps tiles to packets; the decode kernel then gives
+ * one tile to each wave in global tile order, so packets of any size and r
+ * share the GPU as one stream of work.  On a non-NULL stream that is not
+ * already capturing, the three kernels are captured once into a hipGraph
  * (cached per argument set) and replayed on later calls; the number of packets
  * is read on the device, so one graph serves every batch of up to max_packets
- * packets in the same arenas.
+ * packets in the same arenas.  Small batches (by max_packets and the tiles that
+ * cw_words and max_codewords allow) take one or two launches, made directly.
  *   cw_arena, cw_words     : device codeword arena and its size in 64-bit words.
  *   descs                  : device, max_packets descriptors, 8-byte aligned.
  *   n_packets_dev          : device uint32, packets to decode this call

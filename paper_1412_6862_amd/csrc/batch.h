@@ -13,7 +13,8 @@ namespace hm {
 // Head of the caller's workspace.  After it: tile_start[max_packets + 1]
 // (uint64, exclusive prefix sum of tiles per packet), coarse[coarse_cap] and
 // fine[fine_cap] (uint32): coarse[j] is the packet holding tile j << coarse_log2,
-// fine[j] the packet holding tile j << fine_log2 (fine_log2 >= chunk_log2).
+// fine[j] the packet holding tile j << fine_log2 (fine_log2 >= chunk_log2).  A
+// batch uses one of the two maps, or neither when it is decoded in one launch.
 struct BatchWs {
     uint64_t total_tiles;   // tiles of the whole batch
     uint64_t n_packets;     // packets planned (clamped to max_packets)
@@ -86,6 +87,9 @@ inline uint32_t batch_fine_capacity(uint32_t max_packets, uint64_t bytes)
 constexpr uint64_t kWavesPerBlockHost = 4;
 
 hipError_t launch_batch(const BatchArgs& a, int schedule, uint32_t grid, hipStream_t stream);
+
+// Whether launch_batch decodes this batch in one or two launches.
+bool batch_is_short(const BatchArgs& a, uint32_t grid);
 
 // Validate the arguments of hamming_decode_batch, lay the caller's workspace
 // out and size the decode grid.  Returns a status code; *out and *grid are

@@ -9,16 +9,17 @@
 // decoded), so the lookup and its dependent loads are paid per chunk rather
 // than per tile.  Chunks go to waves in order, as the hardware dispatches the
 // plain grid, so the chunks in flight form one advancing window of memory.
-// Four kernels, all replayable from a hipGraph with no host work:
+// The launches, all replayable from a hipGraph with no host work:
 //  * batch_plan_kernel (one workgroup) validates every descriptor, writes its
-//    status and an exclusive prefix sum of its tile count, and picks the
-//    group sizes of two chunk-to-packet maps so that each fits its capacity;
-//  * batch_coarse_kernel fills the coarse map by binary search over the
-//    prefix sums; batch_fine_kernel fills the fine map (normally one entry
-//    per chunk) by a short binary search between two coarse entries;
-//  * decode_batch_kernel reads a chunk's packet from the fine map (plus a
-//    64-lane probe when a fine entry spans several chunks) and decodes it.  A
-//    grid smaller than the batch loops.
+//    status and an exclusive prefix sum of its tile count;
+//    batch_fine_kernel fills the fine map (normally the packet of every chunk)
+//    by searching the prefix sums; decode_batch_kernel reads a chunk's packet
+//    from it (plus a 64-lane probe when a fine entry spans several chunks) and
+//    decodes it.  A grid smaller than the batch loops.
+//  * A batch of fewer packets and chunks takes batch_plan_map_kernel, which adds
+//    a coarse map to the plan, and decode_mapped_batch_kernel, which scans the
+//    prefix sums from there; a short one takes decode_batch_one_kernel alone, in
+//    which every workgroup plans for itself.
 // A batch of at most kSmallBatchMax packets validated by its caller can
 // instead carry its descriptors and tile prefix sums in the kernel arguments
 // of decode_small_batch_kernel: one launch, no copy and no maps, one tile
@@ -49,6 +50,23 @@ struct Schedule {
     static_assert(valid_u(3, U3) && valid_u(4, U4) && valid_u(5, U5) && valid_u(6, U6) && valid_u(7, U7),
                   "invalid lane width");
 };
+
+// How a batch is launched (launch_batch_s), by the packets and the grid that the
+// caller's arguments allow.  A launch after another costs 4-5 us (the gap and
+// the ramp), so short batches take fewer:
+//  * one launch, every workgroup planning for itself, up to kOnePackets packets
+//    and kOneBlocks workgroups (the planning, about 2 us, is paid once per
+//    resident workgroup: 200 packets, 34 MB: 14 us against 16 us with two
+//    launches and 21 with four; 256 packets, 140 MB: 41 against 35);
+//  * two, plan with a coarse map and decode, up to kMapPackets packets and
+//    kMapBlocks workgroups (1000 packets, 47 MB: 19.5 against 24 us), above
+//    which the decode's longer lookup outweighs a launch (2000 packets, 3.7 GB:
+//    decode 618-655 against 584-631 us with the fine map);
+//  * three, plan, fine map and decode.
+constexpr uint32_t kOnePackets = 256;
+constexpr uint32_t kOneBlocks = 4096;
+constexpr uint32_t kMapPackets = 1024;
+constexpr uint32_t kMapBlocks = 16384;
 
 using Sched0 = Schedule<8, 8, 8, 8, 2, 4>;
 using Sched1 = Schedule<8, 4, 4, 4, 2, 5>;
@@ -88,59 +106,81 @@ __device__ int32_t plan_packet(const hamming_packet& d, const BatchArgs& a, uint
     return HAMMING_OK;
 }
 
+// Exclusive prefix sum of t over the THREADS threads of the workgroup; *total
+// receives the sum.  Every thread of the workgroup takes part.
+template <uint32_t THREADS>
+__device__ __forceinline__ uint64_t block_prefix(uint64_t t, uint64_t* total)
+{
+    constexpr uint32_t WAVES = THREADS / 64;
+    __shared__ uint64_t wave_sums[WAVES];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint64_t x = t;   // inclusive scan within the wave
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint64_t y = __shfl_up(x, off);
+        if (lane >= uint32_t(off)) x += y;
+    }
+    if (lane == 63) wave_sums[wave] = x;
+    __syncthreads();
+    uint64_t before = 0, sum = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < WAVES; ++w) {
+        const uint64_t v = wave_sums[w];
+        before += w < wave ? v : 0;
+        sum += v;
+    }
+    __syncthreads();
+    *total = sum;
+    return before + x - t;
+}
+
+// Smallest group size (log2) of at least `least` for which a map of `cap`
+// entries covers `total` tiles: ceil(total / 2^g) <= cap.
+__device__ __forceinline__ uint32_t map_log2(uint64_t total, uint32_t cap, uint32_t least)
+{
+    uint32_t g = least;
+    while ((total >> g) >= cap) ++g;
+    return g;
+}
+
+// Batch totals at the head of the workspace (written by one thread).  The fine
+// map needs at most one entry per chunk (lookups are made at chunk starts only).
+__device__ __forceinline__ void write_totals(const BatchArgs& a, uint64_t total, uint32_t n)
+{
+    const uint32_t gc = map_log2(total, a.coarse_cap, 0), gf = map_log2(total, a.fine_cap, a.chunk_log2);
+    a.ws->total_tiles = total;
+    a.ws->n_packets = n;
+    a.ws->coarse_log2 = gc;
+    a.ws->fine_log2 = gf;
+    a.ws->n_coarse = (total + (uint64_t(1) << gc) - 1) >> gc;
+    a.ws->n_fine = (total + (uint64_t(1) << gf) - 1) >> gf;
+}
+
 template <class S>
 __global__ __launch_bounds__(1024) void batch_plan_kernel(BatchArgs a)
 {
-    __shared__ uint64_t wave_sums[16];
     const uint32_t tid = threadIdx.x;
-    const uint32_t lane = tid & 63u;
-    const uint32_t wave = tid >> 6;
     uint32_t n = *a.n_packets_dev;
     if (n > a.max_packets) n = a.max_packets;
     uint64_t carry = 0;
+    hamming_packet d{};
+    if (tid < n) d = a.descs[tid];
     for (uint32_t base = 0; base < n; base += 1024) {
         const uint32_t p = base + tid;
-        uint64_t t = 0;
+        const hamming_packet cur = d;
+        if (p + 1024 < n) d = a.descs[p + 1024];          // in flight during this scan
+        uint64_t t = 0, sum = 0;
         if (p < n) {
-            const int32_t st = plan_packet<S>(a.descs[p], a, &t);
+            const int32_t st = plan_packet<S>(cur, a, &t);
             if (a.status_out) a.status_out[p] = st;
         }
-        uint64_t x = t;   // inclusive scan within the wave
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint64_t y = __shfl_up(x, off);
-            if (lane >= uint32_t(off)) x += y;
-        }
-        if (lane == 63) wave_sums[wave] = x;
-        __syncthreads();
-        if (wave == 0) {
-            uint64_t v = lane < 16 ? wave_sums[lane] : 0;
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                const uint64_t y = __shfl_up(v, off);
-                if (lane >= uint32_t(off)) v += y;
-            }
-            if (lane < 16) wave_sums[lane] = v;
-        }
-        __syncthreads();
-        const uint64_t before = wave ? wave_sums[wave - 1] : 0;
-        if (p < n) a.tile_start[p] = carry + before + x - t;
-        carry += wave_sums[15];
-        __syncthreads();
+        const uint64_t before = block_prefix<1024>(t, &sum);
+        if (p < n) a.tile_start[p] = carry + before;
+        carry += sum;
     }
     if (tid == 0) {
-        // entries = ceil(total / 2^g) <= capacity; the fine map needs at most
-        // one entry per chunk (lookups are made at chunk starts only)
-        uint32_t gc = 0, gf = a.chunk_log2;
-        while ((carry >> gc) >= a.coarse_cap) ++gc;
-        while ((carry >> gf) >= a.fine_cap) ++gf;
         a.tile_start[n] = carry;
-        a.ws->total_tiles = carry;
-        a.ws->n_packets = n;
-        a.ws->coarse_log2 = gc;
-        a.ws->fine_log2 = gf;
-        a.ws->n_coarse = (carry + (uint64_t(1) << gc) - 1) >> gc;
-        a.ws->n_fine = (carry + (uint64_t(1) << gf) - 1) >> gf;
+        write_totals(a, carry, n);
     }
 }
 
@@ -154,24 +194,69 @@ __device__ __forceinline__ uint32_t search_packet(const uint64_t* ts, uint64_t t
     return lo;
 }
 
-__global__ __launch_bounds__(256) void batch_coarse_kernel(BatchArgs a)
+// The plan of a batch of at most kMapPackets packets together with its coarse
+// map: the prefix sums stay in LDS, where every map entry finds its packet by a
+// binary search.
+template <class S>
+__global__ __launch_bounds__(1024) void batch_plan_map_kernel(BatchArgs a)
 {
-    const uint64_t j = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (j >= a.ws->n_coarse) return;
-    a.coarse[j] = search_packet(a.tile_start, j << a.ws->coarse_log2, 0, uint32_t(a.ws->n_packets));
+    static_assert(kMapPackets == 1024, "one descriptor per thread");
+    __shared__ uint64_t ts[kMapPackets + 1];
+    const uint32_t tid = threadIdx.x;
+    uint32_t n = *a.n_packets_dev;
+    if (n > a.max_packets) n = a.max_packets;
+    uint64_t t = 0, total = 0;
+    if (tid < n) {
+        const int32_t st = plan_packet<S>(a.descs[tid], a, &t);
+        if (a.status_out) a.status_out[tid] = st;
+    }
+    const uint64_t before = block_prefix<1024>(t, &total);
+    if (tid < n) {
+        ts[tid] = before;
+        a.tile_start[tid] = before;
+    }
+    if (tid == 0) {
+        ts[n] = total;
+        a.tile_start[n] = total;
+        write_totals(a, total, n);
+    }
+    __syncthreads();
+    const uint32_t g = map_log2(total, a.coarse_cap, 0);
+    const uint64_t entries = (total + (uint64_t(1) << g) - 1) >> g;
+    for (uint64_t j = tid; j < entries; j += 1024) a.coarse[j] = search_packet(ts, j << g, 0, n);
 }
 
+// Last p in [0, n) with ts[p] <= t, given ts[0] <= t (t uniform across the
+// wave): 64 lanes probe 64 evenly spaced entries per step.
+__device__ __forceinline__ uint32_t wave_search_packet(const uint64_t* ts, uint32_t n, uint64_t t)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t lo = 0, len = n;
+    while (len > 1) {
+        const uint32_t step = (len + 63u) / 64u;
+        const uint32_t q = lo + lane * step;
+        const bool le = lane * step < len && ts[q] <= t;
+        const uint32_t at = uint32_t(__popcll(__ballot(le))) - 1u;    // a prefix of the lanes, lane 0 among them
+        lo += at * step;
+        len = min(step, len - at * step);
+    }
+    return lo;
+}
+
+// The fine map, kFinePerWave consecutive entries per wave: the packets of the
+// first and the last of them bound a short binary search for every entry.
+constexpr uint32_t kFinePerWave = 256;
 __global__ __launch_bounds__(256) void batch_fine_kernel(BatchArgs a)
 {
     const uint64_t n_fine = a.ws->n_fine;
-    const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t j = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < n_fine; j += stride) {
-        const uint64_t t = j << a.ws->fine_log2;
-        const uint64_t jc = t >> a.ws->coarse_log2;
-        const uint32_t lo = a.coarse[jc];
-        // the packet holding tile t lies between the coarse entries around it
-        const uint32_t hi = (jc + 1 < a.ws->n_coarse) ? a.coarse[jc + 1] + 1 : uint32_t(a.ws->n_packets);
-        a.fine[j] = search_packet(a.tile_start, t, lo, hi);
+    const uint32_t g = a.ws->fine_log2, n = uint32_t(a.ws->n_packets), lane = threadIdx.x & 63u;
+    const uint64_t step = uint64_t(gridDim.x) * 4 * kFinePerWave;
+    for (uint64_t first = (uint64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * kFinePerWave;
+         first < n_fine; first += step) {
+        const uint64_t end = first + kFinePerWave < n_fine ? first + kFinePerWave : n_fine;
+        const uint32_t lo = wave_search_packet(a.tile_start, n, first << g);
+        const uint32_t hi = wave_search_packet(a.tile_start, n, (end - 1) << g) + 1u;
+        for (uint64_t j = first + lane; j < end; j += 64) a.fine[j] = search_packet(a.tile_start, j << g, lo, hi);
     }
 }
 
@@ -221,8 +306,8 @@ __device__ __forceinline__ void decode_any_run(const hamming_packet& d, uint64_t
 // Tiles [t, t_end) of the batch in tile order, p being the packet that holds
 // tile t (ts[p] <= t < ts[p + 1]): one run per packet, packets without tiles
 // passed over.  All values are uniform across the wave.
-template <class S>
-__device__ __forceinline__ void decode_span(uint64_t t, uint64_t t_end, uint32_t p, const uint64_t* ts,
+template <class S, class Starts>
+__device__ __forceinline__ void decode_span(uint64_t t, uint64_t t_end, uint32_t p, const Starts& ts,
                                             const hamming_packet* descs, const uint64_t* cw_arena,
                                             uint64_t* data_arena, uint8_t* errpos_arena, uint32_t* lds)
 {
@@ -270,6 +355,58 @@ void decode_batch_kernel(
         if (gf > cl) p = probe_packet(ts, n, t, p);
         const uint64_t t_end = (t + (uint64_t(1) << cl) < total) ? t + (uint64_t(1) << cl) : total;
         decode_span<S>(t, t_end, p, ts, descs, a.cw_arena, a.data_arena, a.errpos_arena, lds);
+    }
+}
+
+// Prefix sums in LDS, read as wave-uniform values.
+struct LdsStarts {
+    const uint64_t* ts;
+    __device__ __forceinline__ uint64_t operator[](uint32_t p) const
+    {
+        const uint64_t v = ts[p];
+        const uint32_t lo = __builtin_amdgcn_readfirstlane(uint32_t(v));
+        return lo | (uint64_t(__builtin_amdgcn_readfirstlane(uint32_t(v >> 32))) << 32);
+    }
+};
+
+// A batch of at most kOnePackets packets in one launch: every workgroup plans
+// the whole batch for itself (a descriptor per thread, the prefix sums in LDS)
+// and then decodes its chunks as decode_batch_kernel does; the first one also
+// writes the statuses and the totals.
+template <class S>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(S::waves_per_simd)))
+void decode_batch_one_kernel(BatchArgs a, const hamming_packet* __restrict__ descs)
+{
+    __shared__ u32x4 lds_raw[kWavesPerBlock][S::LDS_MAX / 4];
+    __shared__ uint64_t starts[kOnePackets + 1];
+    static_assert(kOnePackets == kBlockThreads, "one descriptor per thread");
+    const uint32_t tid = threadIdx.x;
+    uint32_t n = *a.n_packets_dev;
+    if (n > a.max_packets) n = a.max_packets;
+    uint64_t tiles = 0, total = 0;
+    int32_t st = 0;
+    if (tid < n) st = plan_packet<S>(descs[tid], a, &tiles);
+    starts[tid] = block_prefix<kBlockThreads>(tiles, &total);
+    if (tid == 0) starts[n] = total;
+    if (blockIdx.x == 0) {
+        if (tid < n && a.status_out) a.status_out[tid] = st;
+        if (tid == 0) write_totals(a, total, n);
+    }
+    __syncthreads();
+
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    uint32_t* lds = reinterpret_cast<uint32_t*>(&lds_raw[wave][0]);
+    const uint64_t waves = uint64_t(gridDim.x) * kWavesPerBlock;
+    const uint32_t cl = a.chunk_log2;
+    total = LdsStarts{starts}[n];
+    n = __builtin_amdgcn_readfirstlane(n);
+    for (uint64_t c = uint64_t(xcd_block(blockIdx.x, gridDim.x, a.xcd_chunk)) * kWavesPerBlock + wave;
+         (c << cl) < total; c += waves) {
+        const uint64_t t = c << cl;
+        const uint32_t p = probe_packet(starts, n, t, 0);
+        const uint64_t t_end = (t + (uint64_t(1) << cl) < total) ? t + (uint64_t(1) << cl) : total;
+        decode_span<S>(t, t_end, __builtin_amdgcn_readfirstlane(p), LdsStarts{starts}, descs, a.cw_arena, a.data_arena,
+                       a.errpos_arena, lds);
     }
 }
 
@@ -337,6 +474,28 @@ void decode_planned_batch_kernel(PlannedBatch b, const uint64_t* __restrict__ ts
     }
 }
 
+// The same over a device plan (batch_plan_map_kernel): the totals are read
+// first, the packet of a chunk's first tile comes from the coarse map.
+template <class S>
+__global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(S::waves_per_simd)))
+void decode_mapped_batch_kernel(BatchArgs a, const BatchWs* __restrict__ ws, const uint32_t* __restrict__ coarse,
+                                const uint64_t* __restrict__ ts, const hamming_packet* __restrict__ descs)
+{
+    __shared__ u32x4 lds_raw[kWavesPerBlock][S::LDS_MAX / 4];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t* lds = reinterpret_cast<uint32_t*>(&lds_raw[wave][0]);
+    const uint64_t waves = uint64_t(gridDim.x) * kWavesPerBlock;
+    const uint64_t total = ws->total_tiles;
+    const uint32_t n = uint32_t(ws->n_packets), gc = ws->coarse_log2, cl = a.chunk_log2;
+    for (uint64_t c = uint64_t(xcd_block(blockIdx.x, gridDim.x, a.xcd_chunk)) * kWavesPerBlock + wave;
+         (c << cl) < total; c += waves) {
+        const uint64_t t = c << cl;
+        const uint32_t p = scan_packet(ts, n, t, coarse[t >> gc]);
+        const uint64_t t_end = (t + (uint64_t(1) << cl) < total) ? t + (uint64_t(1) << cl) : total;
+        decode_span<S>(t, t_end, p, ts, descs, a.cw_arena, a.data_arena, a.errpos_arena, lds);
+    }
+}
+
 template <class S>
 static hipError_t launch_planned_s(const PlannedBatch& b, hipStream_t stream)
 {
@@ -361,14 +520,28 @@ hipError_t launch_planned_batch(const PlannedBatch& b, int schedule, hipStream_t
     }
 }
 
+static bool one_launch(const BatchArgs& a, uint32_t grid) { return a.max_packets <= kOnePackets && grid <= kOneBlocks; }
+static bool two_launches(const BatchArgs& a, uint32_t grid) { return a.max_packets <= kMapPackets && grid <= kMapBlocks; }
+
+bool batch_is_short(const BatchArgs& a, uint32_t grid) { return one_launch(a, grid) || two_launches(a, grid); }
+
 template <class S>
 static hipError_t launch_batch_s(const BatchArgs& a, uint32_t grid, hipStream_t stream)
 {
+    if (one_launch(a, grid)) {
+        hipLaunchKernelGGL((decode_batch_one_kernel<S>), dim3(grid), dim3(kBlockThreads), 0, stream, a, a.descs);
+        return hipGetLastError();
+    }
+    if (two_launches(a, grid)) {
+        hipLaunchKernelGGL((batch_plan_map_kernel<S>), dim3(1), dim3(1024), 0, stream, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((decode_mapped_batch_kernel<S>), dim3(grid), dim3(kBlockThreads), 0, stream, a, a.ws,
+                           a.coarse, a.tile_start, a.descs);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL((batch_plan_kernel<S>), dim3(1), dim3(1024), 0, stream, a);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(batch_coarse_kernel, dim3((a.coarse_cap + 255) / 256), dim3(256), 0, stream, a);
-    e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(batch_fine_kernel, dim3(a.fine_blocks), dim3(256), 0, stream, a);
     e = hipGetLastError();

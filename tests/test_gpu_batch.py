@@ -420,3 +420,51 @@ def test_batch_full_size_oracle_on_small_and_sampled_packets(full_batch):
         o, e = int(fb["descs"][i]["data_word_off"]) * 8, int(fb["descs"][i]["errpos_off"])
         assert np.array_equal(fb["data"][o:o + d_ref.size], d_ref), "packet %d (r=%d, n=%d)" % (i, rr, n)
         assert np.array_equal(fb["errpos"][e:e + n], e_ref), "packet %d (r=%d, n=%d)" % (i, rr, n)
+
+
+@pytest.mark.parametrize("own_stream", [0, 1])
+@pytest.mark.parametrize("chunk_log2", [0, 3])
+@pytest.mark.parametrize("max_packets,arena_words", [(256, 0), (257, 0), (1024, 0), (1025, 0),
+                                                     (256, 4096 * 2048 + 4096), (1024, 16384 * 2048 + 4096)])
+def test_batch_launch_forms(gpu_device, max_packets, arena_words, chunk_log2, own_stream):
+    """The one-, two- and three-launch forms on either side of their bounds (the
+    packets and the arena that the arguments allow), with fewer packets than
+    max_packets, rejected and empty descriptors; statuses and totals included."""
+    import torch
+
+    n = min(max_packets, 260)
+    arena, descs, ys = _build_batch(max_packets + chunk_log2, n)
+    cw = torch.zeros(max(arena.size, arena_words), dtype=torch.int64, device=gpu_device)
+    cw[:arena.size] = _to_dev(arena, gpu_device)
+    expect = _expect(ys, descs)
+    old_chunk = hm.hamming_batch_chunk_get()
+    hm.hamming_batch_chunk_set(chunk_log2)
+    try:
+        bd = hm.BatchDecoder(cw, max_packets)
+        data_words, errpos_bytes = hm.hamming_batch_layout(descs)
+        bad = {3: ("r", 8), 17: ("flags", 1), n - 2: ("in_word_off", cw.numel() + 1)}
+        want = np.zeros(n, dtype=np.int32)
+        for i, (field, v) in bad.items():
+            descs[i][field] = v
+            if field != "in_word_off":
+                want[i] = hm.HAMMING_EINVAL
+            elif descs[i]["n_cw"]:                 # an empty packet reads nothing
+                want[i] = hm.HAMMING_ERANGE
+        bd.set_packets(descs, layout=False, data_words=data_words, errpos_bytes=errpos_bytes)
+        bd.data.fill_(0x5A5A5A5A5A5A5A5A)
+        bd.errpos.fill_(0xA5)
+        bd.status.fill_(77)
+        s = torch.cuda.Stream() if own_stream else torch.cuda.current_stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            bd.decode(stream=s)
+        torch.cuda.synchronize()
+    finally:
+        hm.hamming_batch_chunk_set(old_chunk)
+    _check_outputs(bd, descs, expect, data_fill=0x5A, ep_fill=0xA5, skip=bad)
+    st = bd.status.cpu().numpy()
+    assert np.array_equal(st[:n], want) and (st[n:] == 77).all()
+    lane = {0: (8, 8, 8, 8, 2), 1: (8, 4, 4, 4, 2), 2: (8, 8, 8, 4, 2), 3: (8, 8, 8, 8, 4)}[hm.hamming_batch_config_get()[0]]
+    tiles = sum(-(-int(d["n_cw"]) // (64 * lane[int(d["r"]) - 3])) for i, d in enumerate(descs) if i not in bad)
+    t = bd.totals()
+    assert t["tiles"] == tiles and t["packets"] == n and t["fine_log2"] == chunk_log2
