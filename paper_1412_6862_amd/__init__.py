@@ -14,6 +14,7 @@ from __future__ import annotations
 import ctypes
 import os
 import threading
+import time
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libhamming.so")
@@ -140,6 +141,8 @@ def library() -> ctypes.CDLL:
     HAMMING_LIB may name another build of the same sources (the sanitizer
     build of the CPU test suite)."""
     global _lib
+    if _lib is not None:        # bound once, under the lock
+        return _lib
     with _lock:
         if _lib is None:
             path = os.environ.get("HAMMING_LIB") or LIB_PATH
@@ -152,7 +155,7 @@ def library() -> ctypes.CDLL:
                 fn.argtypes = args
                 fn.restype = res
             _lib = lib
-    return _lib
+        return _lib
 
 
 def hamming_strerror(status: int) -> str:
@@ -167,6 +170,22 @@ def _check(status: int, where: str) -> None:
         raise HammingError(status, where)
 
 
+def _current_stream() -> int:
+    """torch's current stream, without building a Stream object (0.3 against
+    1.3 us a call)."""
+    import torch
+
+    try:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
+
+
+def _message_stream_bytes(n_cw: int, r: int) -> int:
+    """``hamming_data_bytes`` for the size of a tensor, without a foreign call."""
+    return (n_cw * ((1 << r) - 1 - r) + 63) // 64 * 8 if 3 <= r <= 7 else 0
+
+
 def _ptr(t) -> int:
     if t is None:
         return 0
@@ -177,9 +196,7 @@ def _ptr(t) -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        import torch
-
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -322,10 +339,12 @@ def to_planes(codewords, r: int, stream=None):
     plane_words)."""
     import torch
 
-    cw = codewords.contiguous().view(-1)
+    cw = codewords.contiguous()
     n_cw = cw.numel() // words_per_codeword(r)
     pw = (n_cw + 63) // 64
-    planes = torch.zeros(((1 << r) - 1) * pw, dtype=torch.int64, device=cw.device)
+    planes = torch.empty(((1 << r) - 1) * pw, dtype=torch.int64, device=cw.device)
+    if (n_cw + 31) // 32 % 2:       # the converter writes half of each plane's last word
+        planes.view(-1, pw)[:, -1].zero_()
     hamming_to_planes(cw, n_cw, r, planes, pw, stream)
     return planes, pw
 
@@ -334,7 +353,7 @@ def decode_planes(planes, plane_words: int, n_cw: int, r: int, errpos: bool = Tr
     """Decode a device tensor in the plane layout; returns (data, errpos)."""
     import torch
 
-    data = torch.empty(hamming_data_bytes(n_cw, r), dtype=torch.uint8, device=planes.device)
+    data = torch.empty(_message_stream_bytes(n_cw, r), dtype=torch.uint8, device=planes.device)
     ep = torch.empty(n_cw, dtype=torch.uint8, device=planes.device) if errpos else None
     hamming_decode_planes(planes, plane_words, n_cw, r, data, ep, stream)
     return data, ep
@@ -414,17 +433,19 @@ def decode(codewords, r: int, errpos: bool = True, stream=None):
     """
     import torch
 
-    if codewords.device.type != "cuda":
+    if not codewords.is_cuda:
         raise ValueError("codewords must be a device tensor")
-    cw = codewords.contiguous().view(-1)
-    wpc = words_per_codeword(r)
-    if cw.numel() % wpc:
-        raise ValueError("codeword tensor length is not a multiple of the words per codeword")
-    n_cw = cw.numel() // wpc
-    nbytes = hamming_data_bytes(n_cw, r)
-    data = torch.empty(nbytes, dtype=torch.uint8, device=cw.device)
-    ep = torch.empty(n_cw, dtype=torch.uint8, device=cw.device) if errpos else None
-    hamming_decode(cw, n_cw, r, data, ep, stream)
+    cw = codewords.contiguous()
+    n_cw = cw.numel()
+    if r == 7:
+        if n_cw % 2:
+            raise ValueError("codeword tensor length is not a multiple of the words per codeword")
+        n_cw //= 2
+    dev = cw.device
+    data = torch.empty(_message_stream_bytes(n_cw, r), dtype=torch.uint8, device=dev)
+    ep = torch.empty(n_cw, dtype=torch.uint8, device=dev) if errpos else None
+    _check(library().hamming_decode(cw.data_ptr(), n_cw, r, data.data_ptr(), ep.data_ptr() if errpos else 0,
+                                    _stream(stream)), "hamming_decode")
     return data, ep
 
 
@@ -433,7 +454,7 @@ def encode(messages, n_cw: int, r: int, stream=None):
     stream (at least ceil(n_cw*k/64)*8 bytes); returns int64 codewords."""
     import torch
 
-    if messages.device.type != "cuda":
+    if not messages.is_cuda:
         raise ValueError("messages must be a device tensor")
     out = torch.empty(n_cw * words_per_codeword(r), dtype=torch.int64, device=messages.device)
     hamming_encode(messages.contiguous(), n_cw, r, out, stream)
@@ -493,12 +514,16 @@ class SegmentedBatch:
         self.status = torch.zeros(n_packets, dtype=torch.uint8, device=dev)
 
     def decode(self, stream=None) -> None:
-        hamming_decode_segmented(self.enc, self.enc.numel(), self.descs, self.n_packets, self.msg_bytes, self.msg,
-                                 self.msg.numel(), self.syndromes, self.syndromes.numel(), self.status, stream)
+        _check(library().hamming_decode_segmented(self.enc.data_ptr(), self.enc.numel(), _ptr(self.descs),
+                                                  self.n_packets, self.msg_bytes, self.msg.data_ptr(),
+                                                  self.msg.numel(), self.syndromes.data_ptr(),
+                                                  self.syndromes.numel(), _ptr(self.status), _stream(stream)),
+               "hamming_decode_segmented")
 
     def encode(self, stream=None) -> None:
-        hamming_encode_segmented(self.msg, self.msg.numel(), self.descs, self.n_packets, self.msg_bytes, self.enc,
-                                 self.enc.numel(), stream)
+        _check(library().hamming_encode_segmented(self.msg.data_ptr(), self.msg.numel(), _ptr(self.descs),
+                                                  self.n_packets, self.msg_bytes, self.enc.data_ptr(),
+                                                  self.enc.numel(), _stream(stream)), "hamming_encode_segmented")
 
 
 class BatchDecoder:
@@ -553,9 +578,12 @@ class BatchDecoder:
         return {"tiles": int(q[0]), "packets": int(q[1]), "coarse_log2": int(g[0]), "fine_log2": int(g[1])}
 
     def decode(self, stream=None, max_codewords: int = 0):
-        hamming_decode_batch(self.cw_arena, self.cw_arena.numel(), self.descs_dev, self.n_dev, self.max_packets,
-                             max_codewords, self.data, self.data.numel(), self.errpos, self.errpos.numel(), self.status,
-                             self.workspace, self.ws_bytes, stream)
+        _check(library().hamming_decode_batch(self.cw_arena.data_ptr(), self.cw_arena.numel(),
+                                              _ptr(self.descs_dev), _ptr(self.n_dev), self.max_packets,
+                                              max_codewords, self.data.data_ptr(), self.data.numel(),
+                                              self.errpos.data_ptr(), self.errpos.numel(), _ptr(self.status),
+                                              _ptr(self.workspace), self.ws_bytes, _stream(stream)),
+               "hamming_decode_batch")
 
 
 # ---- autotuning ----------------------------------------------------------------
@@ -659,13 +687,13 @@ class Server:
 
     def result(self, completion, r: int, n_cw: int):
         """(data, errpos) device views of a completed request's outputs."""
-        nbytes = hamming_data_bytes(n_cw, r)
-        return (self.output[completion.data_offset:completion.data_offset + nbytes],
-                self.output[completion.errpos_offset:completion.errpos_offset + n_cw])
+        d, e = completion.data_offset, completion.errpos_offset
+        return self.output[d:d + _message_stream_bytes(n_cw, r)], self.output[e:e + n_cw]
 
     def submit(self, in_word_off: int, n_cw: int, r: int, arrival_ns: int | None = None) -> int:
+        # time.monotonic_ns reads the clock of hamming_server_now_ns
         return hamming_server_submit(self.handle, in_word_off, n_cw, r,
-                                     hamming_server_now_ns() if arrival_ns is None else arrival_ns)
+                                     time.monotonic_ns() if arrival_ns is None else arrival_ns)
 
     def progress(self) -> None:
         hamming_server_progress(self.handle)
