@@ -2,8 +2,7 @@
 // message of codeword i is bits [i*k, i*k+k) of the dense LSB-first stream;
 // the checksum bits follow Sec. III.C.  A thread builds the codewords of one
 // 16-byte output vector at a time (two codewords for r <= 6, one for r = 7)
-// and writes them with one nontemporal 16-byte store when the output is
-// 16-byte aligned.
+// and writes them with one nontemporal 16-byte store.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -12,13 +11,23 @@
 
 namespace hm {
 
-typedef uint32_t enc_u32x4 __attribute__((ext_vector_type(4)));
+// 16-byte vector at 8-byte alignment: a global dwordx4 access needs only dword
+// alignment, so an output at any 64-bit word takes it (64-bit stores at an odd
+// word took 193 us for 2^26 codewords of r = 6 and 185 us for 2^25 of r = 7, the
+// vectors 166 and 169; at a 16-byte boundary 160 and 163).
+typedef uint32_t enc_u32x4 __attribute__((ext_vector_type(4), aligned(8)));
 
 template <int R>
 struct EncShape {
     using C = Code<R>;
     static constexpr int PER = C::WPC == 1 ? 2 : 1;                        // codewords per vector
     static constexpr uint32_t VPT = 2;                                     // vectors per thread (staged)
+    // Vectors per thread of the direct kernel, loaded before the first is built.
+    // The 64 messages of a wave are 256 (r = 3) to 416 bytes (r = 5), so with
+    // one vector in flight a stream that is not in the Infinity Cache came at
+    // less than 1 TB/s (r = 4, 2^26 codewords: 126 us against 107 with four, 90
+    // against 85 where it is; eight: 110, 95).  r = 3 gains nothing (82 us).
+    static constexpr uint32_t DIRECT = R == 3 ? 1 : 4;
     static constexpr uint32_t CW = 256u * PER * VPT;                       // codewords per tile (staged)
     static constexpr uint32_t LDS_Q = (CW * C::K) / 64 + C::PW / 2 + 3;    // staged 64-bit words
 };
@@ -42,11 +51,11 @@ __device__ __forceinline__ void build_codeword(const uint32_t (&raw)[Code<R>::PW
 // n_cw are not written.
 template <int R>
 __device__ __forceinline__ void store_vector(const uint32_t (&a)[EncShape<R>::PER][Code<R>::DW], uint64_t j,
-                                             uint64_t n_cw, uint32_t out16, uint64_t* __restrict__ cw_out)
+                                             uint64_t n_cw, uint64_t* __restrict__ cw_out)
 {
     using C = Code<R>;
     constexpr int PER = EncShape<R>::PER;
-    if (out16 && (j + 1) * PER <= n_cw) {
+    if ((j + 1) * PER <= n_cw) {
         enc_u32x4 v;
         v.x = a[0][0];
         v.y = a[0][1];
@@ -69,28 +78,38 @@ __device__ __forceinline__ void store_vector(const uint32_t (&a)[EncShape<R>::PE
 template <int R>
 __global__ __launch_bounds__(256) void encode_plain_kernel(const uint32_t* __restrict__ stream,
                                                            uint64_t stream_dwords, uint64_t n_cw,
-                                                           uint64_t* __restrict__ cw_out, uint32_t out16)
+                                                           uint64_t* __restrict__ cw_out)
 {
     using C = Code<R>;
     constexpr int PER = EncShape<R>::PER;
-    const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
+    constexpr uint32_t VPT = EncShape<R>::DIRECT;
     const uint64_t n_vec = (n_cw + PER - 1) / PER;
-    for (uint64_t j = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; j < n_vec; j += stride) {
-        uint32_t a[PER][C::DW];
+    const uint64_t step = uint64_t(gridDim.x) * 256 * VPT;
+    for (uint64_t first = uint64_t(blockIdx.x) * 256 * VPT + threadIdx.x; first < n_vec; first += step) {
+        uint32_t raw[VPT][PER][C::PW + 1], sh[VPT][PER];
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-            const uint64_t o = (j * PER + u) * C::K;
-            const uint64_t d = o >> 5;
-            uint32_t raw[C::PW + 1];
+        for (uint32_t v = 0; v < VPT; ++v) {
 #pragma unroll
-            for (int q = 0; q <= C::PW; ++q) raw[q] = (d + q < stream_dwords) ? stream[d + q] : 0u;
-            build_codeword<R>(raw, uint32_t(o & 31u), a[u]);
+            for (int u = 0; u < PER; ++u) {
+                const uint64_t o = ((first + 256 * v) * PER + u) * C::K;
+                const uint64_t d = o >> 5;
+                sh[v][u] = uint32_t(o & 31u);
+#pragma unroll
+                for (int q = 0; q <= C::PW; ++q) raw[v][u][q] = stream[d + q < stream_dwords ? d + q : stream_dwords - 1];
+            }
         }
-        store_vector<R>(a, j, n_cw, out16, cw_out);
+#pragma unroll
+        for (uint32_t v = 0; v < VPT; ++v) {
+            if (first + 256 * v >= n_vec) break;
+            uint32_t a[PER][C::DW];
+#pragma unroll
+            for (int u = 0; u < PER; ++u) build_codeword<R>(raw[v][u], sh[v][u], a[u]);
+            store_vector<R>(a, first + 256 * v, n_cw, cw_out);
+        }
     }
 }
 
-// ---- long messages (r = 6, 7): the stream is staged through LDS ------------
+// ---- long messages (r = 6, 7, large r = 5): the stream is staged in LDS ------------
 // A workgroup of 256 threads encodes one tile of 512 output vectors (two per
 // thread, 256 apart, so stores stay coalesced).  The tile's slice of the
 // message stream is staged in LDS with coalesced 64-bit loads; each thread
@@ -101,8 +120,7 @@ __global__ __launch_bounds__(256) void encode_plain_kernel(const uint32_t* __res
 // masked off or belong to no codeword).
 template <int R>
 __global__ __launch_bounds__(256) void encode_staged_kernel(const uint64_t* __restrict__ stream, uint64_t stream_q,
-                                                            uint64_t n_cw, uint64_t* __restrict__ cw_out,
-                                                            uint32_t out16)
+                                                            uint64_t n_cw, uint64_t* __restrict__ cw_out)
 {
     using C = Code<R>;
     using S = EncShape<R>;
@@ -148,7 +166,7 @@ __global__ __launch_bounds__(256) void encode_staged_kernel(const uint64_t* __re
                 for (int q = 0; q <= C::PW; ++q) raw[q] = src[q];
                 build_codeword<R>(raw, uint32_t(o & 31u), a[u]);
             }
-            store_vector<R>(a, j, n_cw, out16, cw_out);
+            store_vector<R>(a, j, n_cw, cw_out);
         }
     }
 }
@@ -160,26 +178,35 @@ __global__ __launch_bounds__(256) void encode_staged_kernel(const uint64_t* __re
 constexpr uint64_t kEncodeMaxBlocks = 32768;
 constexpr uint64_t kEncodeDirectMaxBlocks = 65536;
 
+// Message streams of r = 5 above this are staged too.  The direct kernel reads
+// through the caches and is faster where the stream is in the Infinity Cache
+// (2^26 codewords, 208 MiB: 105 against 120 us; 2^25: 54 against 61), the staged
+// one is the same either way (2^26, not cached: 120 against 153 us; 2^25: 61
+// against 78); beyond half of the 256 MB the stream is rarely there.
+constexpr uint64_t kEncodeCachedBytes = uint64_t(128) << 20;
+
 template <int R>
 static hipError_t launch_encode_r(const void* stream_in, uint64_t n_cw, uint64_t* out, hipStream_t stream)
 {
     using C = Code<R>;
     const uint64_t stream_q = (n_cw * C::K + 63) / 64;
-    const uint32_t out16 = (reinterpret_cast<uintptr_t>(out) & 15u) == 0 ? 1u : 0u;
-    if constexpr (R >= 6) {
-        using T = EncShape<R>;
-        uint64_t blocks = (n_cw + T::CW - 1) / T::CW;
-        if (blocks > kEncodeMaxBlocks) blocks = kEncodeMaxBlocks;
-        if (blocks == 0) return hipSuccess;
-        hipLaunchKernelGGL((encode_staged_kernel<R>), dim3(uint32_t(blocks)), dim3(256), 0, stream,
-                           static_cast<const uint64_t*>(stream_in), stream_q, n_cw, out, out16);
-    } else {
+    if (R >= 6 || (R == 5 && stream_q * 8 > kEncodeCachedBytes)) {
+        if constexpr (R >= 5) {
+            using T = EncShape<R>;
+            uint64_t blocks = (n_cw + T::CW - 1) / T::CW;
+            if (blocks > kEncodeMaxBlocks) blocks = kEncodeMaxBlocks;
+            if (blocks == 0) return hipSuccess;
+            hipLaunchKernelGGL((encode_staged_kernel<R>), dim3(uint32_t(blocks)), dim3(256), 0, stream,
+                               static_cast<const uint64_t*>(stream_in), stream_q, n_cw, out);
+        }
+    } else if constexpr (R <= 5) {
         constexpr uint64_t per = EncShape<R>::PER;
-        uint64_t blocks = ((n_cw + per - 1) / per + 255) / 256;
+        constexpr uint64_t per_block = 256 * EncShape<R>::DIRECT;
+        uint64_t blocks = ((n_cw + per - 1) / per + per_block - 1) / per_block;
         if (blocks > kEncodeDirectMaxBlocks) blocks = kEncodeDirectMaxBlocks;
         if (blocks == 0) return hipSuccess;
         hipLaunchKernelGGL((encode_plain_kernel<R>), dim3(uint32_t(blocks)), dim3(256), 0, stream,
-                           static_cast<const uint32_t*>(stream_in), 2 * stream_q, n_cw, out, out16);
+                           static_cast<const uint32_t*>(stream_in), 2 * stream_q, n_cw, out);
     }
     return hipGetLastError();
 }

@@ -325,3 +325,37 @@ def test_plain_parity_2p28_sampled(gpu_device, r):
         assert np.array_equal(data[b0:b0 + d_ref.size].cpu().numpy(), d_ref), first
         assert np.array_equal(ep[first:first + n].cpu().numpy(), e_ref), first
     assert data.numel() == hm.hamming_data_bytes(n_cw, r)
+
+
+@pytest.mark.parametrize("r", [4, 5])
+@pytest.mark.parametrize("n_cw", [1, 511, 513, 2047, 2048, 2049, 6145])
+def test_encode_parity_odd_output_word_around_blocks(gpu_device, r, n_cw):
+    """Short messages at an odd output word around a block's 2048 codewords;
+    the words around the output stay untouched."""
+    import torch
+
+    stream = synth.message_stream(synth.workload_seed("gpu-enc-odd", r, n_cw), n_cw, r)
+    buf = torch.full((n_cw + 2,), 0x5A5A5A5A5A5A5A5A, dtype=torch.int64, device=gpu_device)
+    out = buf[1:1 + n_cw]
+    assert out.data_ptr() % 16 == 8
+    hm.hamming_encode(to_device(stream, gpu_device), n_cw, r, out)
+    torch.cuda.synchronize()
+    host = buf.cpu().numpy().view(np.uint64)
+    assert np.array_equal(host[1:-1], oracle.encode(stream, n_cw, r))
+    assert host[0] == host[-1] == 0x5A5A5A5A5A5A5A5A
+
+
+@pytest.mark.parametrize("n_cw", [41297762, 41297763])
+def test_encode_large_hamming_31_26_either_form(gpu_device, n_cw):
+    """A message stream of exactly 128 MiB (read directly) and one just above
+    (staged) against the two halves encoded on their own."""
+    import torch
+
+    stream = synth.message_stream_torch(synth.workload_seed("gpu-enc-large", 5), n_cw, 5, gpu_device)
+    assert (stream.numel() * 8 > 128 << 20) == (n_cw > 41297762)
+    whole = hm.encode(stream, n_cw, 5)
+    half = n_cw // 2 // 64 * 64
+    a = hm.encode(stream, half, 5)
+    b = hm.encode(stream[half * 26 // 64:].clone(), n_cw - half, 5)
+    torch.cuda.synchronize()
+    assert torch.equal(whole[:half], a) and torch.equal(whole[half:], b)
