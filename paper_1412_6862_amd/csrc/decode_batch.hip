@@ -277,7 +277,7 @@ __device__ __forceinline__ uint32_t probe_packet(const uint64_t* ts, uint32_t n,
 }
 
 // Tiles [tl0, tl1) of one packet as one pipelined run.
-template <int R, int U>
+template <int R, int U, bool NT>
 __device__ __forceinline__ void decode_packet_run(const hamming_packet& d, uint64_t tl0, uint64_t tl1,
                                                   const uint64_t* cw_arena, uint64_t* data_arena,
                                                   uint8_t* errpos_arena, uint32_t* lds)
@@ -286,27 +286,27 @@ __device__ __forceinline__ void decode_packet_run(const hamming_packet& d, uint6
     uint64_t* data = data_arena + d.data_word_off;
     uint8_t* ep = (d.errpos_off == HAMMING_NO_ERRPOS) ? nullptr : errpos_arena + d.errpos_off;
     const uint32_t flags = (ep && (reinterpret_cast<uintptr_t>(ep) % U) == 0) ? kFlagEpVec : 0u;
-    decode_run<R, U>(cw, d.n_cw, tl0, tl1, 1, data, message_words(d.n_cw, R), ep, lds, flags);
+    decode_run<R, U, NT>(cw, d.n_cw, tl0, tl1, 1, data, message_words(d.n_cw, R), ep, lds, flags);
 }
 
-template <class S>
+template <class S, bool NT>
 __device__ __forceinline__ void decode_any_run(const hamming_packet& d, uint64_t tl0, uint64_t tl1,
                                                const uint64_t* cw_arena, uint64_t* data_arena,
                                                uint8_t* errpos_arena, uint32_t* lds)
 {
     switch (d.r) {
-    case 3: decode_packet_run<3, S::u[0]>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
-    case 4: decode_packet_run<4, S::u[1]>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
-    case 5: decode_packet_run<5, S::u[2]>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
-    case 6: decode_packet_run<6, S::u[3]>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
-    default: decode_packet_run<7, S::u[4]>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
+    case 3: decode_packet_run<3, S::u[0], NT>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
+    case 4: decode_packet_run<4, S::u[1], NT>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
+    case 5: decode_packet_run<5, S::u[2], NT>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
+    case 6: decode_packet_run<6, S::u[3], NT>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
+    default: decode_packet_run<7, S::u[4], NT>(d, tl0, tl1, cw_arena, data_arena, errpos_arena, lds); break;
     }
 }
 
 // Tiles [t, t_end) of the batch in tile order, p being the packet that holds
 // tile t (ts[p] <= t < ts[p + 1]): one run per packet, packets without tiles
 // passed over.  All values are uniform across the wave.
-template <class S, class Starts>
+template <class S, bool NT, class Starts>
 __device__ __forceinline__ void decode_span(uint64_t t, uint64_t t_end, uint32_t p, const Starts& ts,
                                             const hamming_packet* descs, const uint64_t* cw_arena,
                                             uint64_t* data_arena, uint8_t* errpos_arena, uint32_t* lds)
@@ -317,7 +317,7 @@ __device__ __forceinline__ void decode_span(uint64_t t, uint64_t t_end, uint32_t
             const hamming_packet d = descs[p];
             const uint64_t t0 = ts[p];
             const uint64_t e = t1 < t_end ? t1 : t_end;
-            decode_any_run<S>(d, t - t0, e - t0, cw_arena, data_arena, errpos_arena, lds);
+            decode_any_run<S, NT>(d, t - t0, e - t0, cw_arena, data_arena, errpos_arena, lds);
             t = e;
         }
         ++p;
@@ -354,7 +354,7 @@ void decode_batch_kernel(
         first = false;
         if (gf > cl) p = probe_packet(ts, n, t, p);
         const uint64_t t_end = (t + (uint64_t(1) << cl) < total) ? t + (uint64_t(1) << cl) : total;
-        decode_span<S>(t, t_end, p, ts, descs, a.cw_arena, a.data_arena, a.errpos_arena, lds);
+        decode_span<S, true>(t, t_end, p, ts, descs, a.cw_arena, a.data_arena, a.errpos_arena, lds);
     }
 }
 
@@ -405,7 +405,7 @@ void decode_batch_one_kernel(BatchArgs a, const hamming_packet* __restrict__ des
         const uint64_t t = c << cl;
         const uint32_t p = probe_packet(starts, n, t, 0);
         const uint64_t t_end = (t + (uint64_t(1) << cl) < total) ? t + (uint64_t(1) << cl) : total;
-        decode_span<S>(t, t_end, __builtin_amdgcn_readfirstlane(p), LdsStarts{starts}, descs, a.cw_arena, a.data_arena,
+        decode_span<S, false>(t, t_end, __builtin_amdgcn_readfirstlane(p), LdsStarts{starts}, descs, a.cw_arena, a.data_arena,
                        a.errpos_arena, lds);
     }
 }
@@ -425,7 +425,7 @@ void decode_small_batch_kernel(SmallBatch b)
     uint32_t p = 0;
     while (p + 1 < b.n && b.tile_start[p + 1] <= t) ++p;    // packets without tiles are passed over
     const hamming_packet d = b.descs[p];
-    decode_any_run<S>(d, t - b.tile_start[p], t + 1 - b.tile_start[p], b.cw_arena, b.data_arena, b.errpos_arena,
+    decode_any_run<S, false>(d, t - b.tile_start[p], t + 1 - b.tile_start[p], b.cw_arena, b.data_arena, b.errpos_arena,
                       lds);
 }
 
@@ -470,7 +470,7 @@ void decode_planned_batch_kernel(PlannedBatch b, const uint64_t* __restrict__ ts
         const uint64_t t = c << cl;
         const uint32_t p = scan_packet(ts, b.n, t, coarse[t >> b.coarse_log2]);
         const uint64_t t_end = (t + (uint64_t(1) << cl) < b.total_tiles) ? t + (uint64_t(1) << cl) : b.total_tiles;
-        decode_span<S>(t, t_end, p, ts, descs, b.cw_arena, b.data_arena, b.errpos_arena, lds);
+        decode_span<S, true>(t, t_end, p, ts, descs, b.cw_arena, b.data_arena, b.errpos_arena, lds);
     }
 }
 
@@ -492,7 +492,7 @@ void decode_mapped_batch_kernel(BatchArgs a, const BatchWs* __restrict__ ws, con
         const uint64_t t = c << cl;
         const uint32_t p = scan_packet(ts, n, t, coarse[t >> gc]);
         const uint64_t t_end = (t + (uint64_t(1) << cl) < total) ? t + (uint64_t(1) << cl) : total;
-        decode_span<S>(t, t_end, p, ts, descs, a.cw_arena, a.data_arena, a.errpos_arena, lds);
+        decode_span<S, true>(t, t_end, p, ts, descs, a.cw_arena, a.data_arena, a.errpos_arena, lds);
     }
 }
 

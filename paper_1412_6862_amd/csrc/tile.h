@@ -117,6 +117,17 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// One 16-byte input vector: nontemporal (NT), or through the caches for inputs
+// that may still lie in the Infinity Cache.
+template <bool NT>
+__device__ __forceinline__ u32x4 load_vector(const u32x4a8* p)
+{
+    if constexpr (NT)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
 // Input registers of one lane for one tile: the lane's 16-byte vectors
 // v*64 + lane of the tile (consecutive lanes read consecutive vectors);
 // finish_tile transposes them through LDS to the lane's own U codewords.
@@ -129,7 +140,7 @@ struct TileIn {
 // vectors past its last codeword read as zero (a vector holding only the
 // last word is read as one 8-byte load), so every access stays inside the
 // packet and the tile still goes through the coalesced transpose.
-template <int R, int U>
+template <int R, int U, bool NT>
 __device__ __forceinline__ void load_tile(const uint64_t* __restrict__ cw, uint64_t n_cw, uint64_t tile,
                                           uint32_t lane, TileIn<R, U>& t)
 {
@@ -140,7 +151,7 @@ __device__ __forceinline__ void load_tile(const uint64_t* __restrict__ cw, uint6
     if ((tile + 1) * T::CW <= n_cw) {
 #pragma unroll
         for (int v = 0; v < T::NV; ++v) {
-            const u32x4 x = __builtin_nontemporal_load(src + 64 * v);
+            const u32x4 x = load_vector<NT>(src + 64 * v);
             t.in[4 * v + 0] = x.x;
             t.in[4 * v + 1] = x.y;
             t.in[4 * v + 2] = x.z;
@@ -153,7 +164,7 @@ __device__ __forceinline__ void load_tile(const uint64_t* __restrict__ cw, uint6
             const uint64_t w = 2 * (64u * uint64_t(v) + lane);   // first word of this lane's vector v
             u32x4 x = {0u, 0u, 0u, 0u};
             if (w + 1 < rem) {
-                x = __builtin_nontemporal_load(src + 64 * v);
+                x = load_vector<NT>(src + 64 * v);
             } else if (w < rem) {
                 const uint64_t y = cw[w0 + w];
                 x.x = uint32_t(y);
@@ -169,7 +180,7 @@ __device__ __forceinline__ void load_tile(const uint64_t* __restrict__ cw, uint6
 
 // Issue the loads of a tile known to be full (the vector form of load_tile
 // with no checks).
-template <int R, int U>
+template <int R, int U, bool NT>
 __device__ __forceinline__ void load_full_tile(const uint64_t* __restrict__ cw, uint64_t tile, uint32_t lane,
                                                TileIn<R, U>& t)
 {
@@ -178,7 +189,7 @@ __device__ __forceinline__ void load_full_tile(const uint64_t* __restrict__ cw, 
     const u32x4a8* src = reinterpret_cast<const u32x4a8*>(cw + tile * T::CW * C::WPC) + lane;
 #pragma unroll
     for (int v = 0; v < T::NV; ++v) {
-        const u32x4 x = __builtin_nontemporal_load(src + 64 * v);
+        const u32x4 x = load_vector<NT>(src + 64 * v);
         t.in[4 * v + 0] = x.x;
         t.in[4 * v + 1] = x.y;
         t.in[4 * v + 2] = x.z;
@@ -321,13 +332,13 @@ __device__ __forceinline__ void finish_tile(TileIn<R, U>& tin, uint64_t n_cw, ui
     wave_sync();
 }
 
-template <int R, int U>
+template <int R, int U, bool NT>
 __device__ __forceinline__ void decode_tile(const uint64_t* __restrict__ cw, uint64_t n_cw, uint64_t tile,
                                             uint32_t lane, uint64_t* __restrict__ data, uint64_t data_words,
                                             uint8_t* __restrict__ errpos, uint32_t* lds, uint32_t flags)
 {
     TileIn<R, U> t;
-    load_tile<R, U>(cw, n_cw, tile, lane, t);
+    load_tile<R, U, NT>(cw, n_cw, tile, lane, t);
     finish_tile<R, U>(t, n_cw, tile, lane, data, data_words, errpos, lds, flags);
 }
 
@@ -347,7 +358,7 @@ __device__ __forceinline__ uint32_t run_lane()
 // it decodes the current one, so two tiles of loads are in flight while it
 // computes.  Tiles past the last full one (at most the ragged tile) go
 // through the checked path.
-template <int R, int U>
+template <int R, int U, bool NT>
 __device__ __forceinline__ void decode_run(const uint64_t* __restrict__ cw, uint64_t n_cw, uint64_t t,
                                            uint64_t t_end, uint64_t stride, uint64_t* __restrict__ data,
                                            uint64_t data_words, uint8_t* __restrict__ errpos, uint32_t* lds,
@@ -359,12 +370,12 @@ __device__ __forceinline__ void decode_run(const uint64_t* __restrict__ cw, uint
     const uint64_t full_end = t_end < n_full ? t_end : n_full;
     if (t < full_end) {
         TileIn<R, U> cur;
-        load_full_tile<R, U>(cw, t, lane, cur);
+        load_full_tile<R, U, NT>(cw, t, lane, cur);
         for (;;) {
             const uint64_t tn = t + stride;
             if (tn >= full_end) break;
             TileIn<R, U> nxt;
-            load_full_tile<R, U>(cw, tn, lane, nxt);    // in flight while `cur` is decoded
+            load_full_tile<R, U, NT>(cw, tn, lane, nxt);    // in flight while `cur` is decoded
             finish_tile<R, U>(cur, n_cw, t, lane, data, data_words, errpos, lds, flags);
             cur = nxt;
             t = tn;
@@ -372,7 +383,7 @@ __device__ __forceinline__ void decode_run(const uint64_t* __restrict__ cw, uint
         finish_tile<R, U>(cur, n_cw, t, lane, data, data_words, errpos, lds, flags);
         t += stride;
     }
-    for (; t < t_end; t += stride) decode_tile<R, U>(cw, n_cw, t, lane, data, data_words, errpos, lds, flags);
+    for (; t < t_end; t += stride) decode_tile<R, U, NT>(cw, n_cw, t, lane, data, data_words, errpos, lds, flags);
 }
 
 }  // namespace hm

@@ -359,3 +359,28 @@ def test_encode_large_hamming_31_26_either_form(gpu_device, n_cw):
     b = hm.encode(stream[half * 26 // 64:].clone(), n_cw - half, 5)
     torch.cuda.synchronize()
     assert torch.equal(whole[:half], a) and torch.equal(whole[half:], b)
+
+
+@pytest.mark.parametrize("r", [3, 6, 7])
+def test_decode_either_side_of_the_cached_size(gpu_device, r):
+    """A packet of 64 MiB of input (read through the caches) and one of a word
+    more (nontemporal): the common codewords decode alike, and slices at both
+    ends and at the boundary equal the oracle's."""
+    import torch
+
+    wpc, k = hm.words_per_codeword(r), hm.hamming_message_bits(r)
+    n = (64 << 20) // (8 * wpc)
+    seed = synth.workload_seed("gpu-plain-cached", r)
+    cw = hm.encode(synth.message_stream_torch(seed, n + 1, r, gpu_device), n + 1, r)
+    cw ^= synth.flip_masks_torch(seed, n + 1, r, 0.3, gpu_device)
+    d, e = hm.decode(cw[:n * wpc], r)
+    d1, e1 = hm.decode(cw, r)
+    torch.cuda.synchronize()
+    assert torch.equal(e1[:n], e) and torch.equal(d1[:n * k // 8], d[:n * k // 8])
+    for first in (0, n - 128):
+        y = cw[first * wpc:(first + 128) * wpc].cpu().numpy().view(np.uint64)
+        d_ref, e_ref = oracle.decode(y, r)
+        assert np.array_equal(d[first * k // 8:first * k // 8 + d_ref.size].cpu().numpy(), d_ref)
+        assert np.array_equal(e[first:first + 128].cpu().numpy(), e_ref)
+    d_ref, e_ref = oracle.decode(cw[(n - 63) * wpc:].cpu().numpy().view(np.uint64), r)
+    assert np.array_equal(e1[n - 63:].cpu().numpy(), e_ref)
