@@ -911,6 +911,11 @@ uint32_t auto_threads_per_packet(uint32_t n_packets, uint32_t max_msg_bytes, boo
     // 640 bytes 127 against 141 us, 800 bytes 176-180 against 158-161.  From
     // there 16 win up to 2000 bytes (339 us, 32: 344) for every t
     if (max_msg_bytes <= (decode ? 640u : 704u)) return 8u;
+    // Up to 4096 packets 16 lanes each leave a SIMD one wave, 32 two.  Decode
+    // and encode, 32 against 16: 4096 equal packets of 2000 bytes 6.8 and 7.0
+    // against 7.9 and 7.7 us, 400..2000 bytes 7.3 and 8.1 against 8.4 and 9.4;
+    // at 1200 bytes (5.9 and 6.2) and with 6000 packets no difference.
+    if (n_packets <= 4096 && max_msg_bytes > 1000 && max_msg_bytes <= 2048) return 32u;
     return max_msg_bytes <= 2048 ? 16u : (max_msg_bytes <= 3072 ? 32u : 64u);
 }
 

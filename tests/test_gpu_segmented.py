@@ -446,3 +446,42 @@ def test_segmented_equal_packets_at_a_stride(gpu_device, seg_mode, msg_bytes, t,
     torch.cuda.synchronize()
     want = oracle.seg_encode_many(msgs, t, row_bytes=8 * ew)
     assert np.array_equal(enc_t.cpu().numpy().view(np.uint64), arena(want, ew, es, 3))
+
+
+@pytest.mark.parametrize("P,msg_bytes", [(2048, 1001), (2049, 1000), (2049, 1001), (4096, 2048), (4096, 2049),
+                                         (4097, 2048)])
+def test_segmented_automatic_group_edges(gpu_device, P, msg_bytes):
+    """Both directions at the edges of the automatic choice of lanes."""
+    import torch
+
+    t = 5
+    bits = oracle.seg_layout(msg_bytes, t)[3]
+    ew, mw = (bits + 63) // 64, (msg_bytes + 7) // 8
+    seed = synth.workload_seed("gpu-seg-auto", msg_bytes, t)
+    enc = _received(seed, P, msg_bytes, t, 8 * ew, 0.4, 0.2)
+    msgs = synth.packet_bytes(seed, P, msg_bytes)
+    d = np.zeros(P, dtype=hm.seg_packet_dtype())
+    q = np.arange(P, dtype=np.uint64)
+    d["enc_word_off"], d["msg_word_off"], d["seg_off"] = q * np.uint64(ew), q * np.uint64(mw), q * np.uint64(t)
+    d["msg_bytes"], d["t"] = msg_bytes, t
+    desc = torch.from_numpy(d.view(np.uint8)).to(gpu_device)
+    enc_t = torch.from_numpy(np.ascontiguousarray(enc).view(np.int64).reshape(-1)).to(gpu_device)
+    msg_t = torch.zeros(P * mw, dtype=torch.int64, device=gpu_device)
+    syn = torch.zeros(P * t, dtype=torch.int16, device=gpu_device)
+    st = torch.zeros(P, dtype=torch.uint8, device=gpu_device)
+    hm.hamming_decode_segmented(enc_t, enc_t.numel(), desc, P, msg_bytes, msg_t, msg_t.numel(), syn, syn.numel(), st)
+    torch.cuda.synchronize()
+    m_ref, s_ref, st_ref = oracle.seg_decode_many(enc, msg_bytes, t)
+    got = msg_t.cpu().numpy().view(np.uint8).reshape(P, 8 * mw)
+    assert np.array_equal(got[:, :msg_bytes], m_ref)
+    assert np.array_equal(syn.cpu().numpy().view(np.uint16).reshape(P, t), s_ref)
+    assert np.array_equal(st.cpu().numpy(), st_ref)
+
+    rows = np.zeros((P, 8 * mw), dtype=np.uint8)
+    rows[:, :msg_bytes] = msgs
+    msg_t = torch.from_numpy(rows.view(np.int64).reshape(-1)).to(gpu_device)
+    enc_t = torch.zeros(P * ew, dtype=torch.int64, device=gpu_device)
+    hm.hamming_encode_segmented(msg_t, msg_t.numel(), desc, P, msg_bytes, enc_t, enc_t.numel())
+    torch.cuda.synchronize()
+    want = oracle.seg_encode_many(msgs, t, row_bytes=8 * ew)
+    assert np.array_equal(enc_t.cpu().numpy().view(np.uint8).reshape(P, 8 * ew), want)
