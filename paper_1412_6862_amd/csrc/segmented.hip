@@ -485,13 +485,13 @@ __device__ __forceinline__ void encode_packet(const SegArgs& a, const hamming_se
 
 // ---- part form ---------------------------------------------------------------
 //
-// The packets of a wave that have one shape and lie at one stride in either
-// arena (a batch of equal packets, end to end or with a gap after each) take
-// this form: their words are one run, which the 64 lanes copy into LDS and the
-// results out of it in whole cache lines.  The bits are then dealt by segment: every lane owns one part
-// of one segment (seg_parts.h), reads it from LDS into registers, folds its
-// syndrome there and ORs its message (or encoded) bits into place over the run
-// it came from.
+// The packets of a wave that lie end to end in both arenas, or have one shape
+// and lie at one stride in either (a gap after each), take this form: their
+// words are one run, which the 64 lanes copy into LDS and the results out of it
+// in whole cache lines.  The bits are then dealt by segment: every lane owns
+// one part of one segment (seg_parts.h), reads it from LDS into registers,
+// folds its syndrome there and ORs its message (or encoded) bits into place
+// over the run it came from.
 //
 // What bounded the window form was neither its instructions nor its latency
 // but how its loads met the memory: a group's loads start wherever its packet
@@ -499,7 +499,10 @@ __device__ __forceinline__ void encode_packet(const SegArgs& a, const hamming_se
 // A copy of the kernel with all bit work taken out ran no faster (1200-byte
 // packets, t = 4, 2^19 of them: 253-285 us, decoding 256-281 us); moving the
 // same words as one run per wave, with the bit work, takes 200 us (6.4 TB/s).
-// Encoding 2^18 packets of 800 bytes, t = 5: 104 -> 75 us (5.7 TB/s).
+// Encoding 2^18 packets of 800 bytes, t = 5: 104 -> 75 us (5.7 TB/s).  Packets of
+// several shapes hold their layout per lane instead of per wave, and a lane
+// waits for the longest part: 2^18 of 400 to 2000 bytes, t = 2 to 6, decode
+// 181 -> 141 us, encode 204 -> 148; of 400 to 800 bytes 98 -> 88, 106 -> 77.
 
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
 
@@ -649,12 +652,15 @@ __device__ __forceinline__ void or_window(uint32_t* p, const hm::Placed& w)
     for (int k = 0; k < 5; ++k) atomicOr(p + w.first + k, w.y[k]);
 }
 
-// The packets of a wave: their layout and parts, encoded and message words,
-// the words from one packet to the next (es, ms) and the first words of their
-// runs.  W is the wave's LDS and X (within it) one syndrome per lane.
+// The packets of a wave: this lane's packet's layout, parts and first word in
+// either run (e0, m0), the most windows of a part (len), the words of the runs
+// and their first words, and for packets with gaps between them (packet !=
+// stride) the words of one and from one to the next.  W is the wave's LDS and
+// X (within it) one syndrome per lane.
 struct WaveRun {
     Layout Lo;
     hm::Parts P;
+    uint32_t e0, m0, len, eruns, mruns;
     uint32_t ew, mw, es, ms;
     uint64_t *enc, *msg;
     uint32_t *W, *X;
@@ -671,8 +677,8 @@ __device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r,
     const hm::Parts& P = r.P;
     uint32_t* S = r.W;
     uint32_t* X = r.X + slot * GROUP;
-    const Run in(r.enc, (64 / GROUP - 1) * r.es + r.ew), out(r.msg, (64 / GROUP - 1) * r.ms + r.mw);
-    const uint32_t mb = out.at(slot * r.ms);
+    const Run in(r.enc, r.eruns), out(r.msg, r.mruns);
+    const uint32_t mb = out.at(r.m0);
     X[gl] = 0;
     if (a.cached)
         in.load<false>(r.enc, S, lane);
@@ -681,15 +687,16 @@ __device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r,
     wave_sync();
 
     const Part pt(Lo, P, gl);
-    const uint32_t bit = pt.o + 128u * pt.v0 + 32u * in.at(slot * r.es) - 1u;   // LDS bit of position 128 v0
+    const uint32_t bit = pt.o + 128u * pt.v0 + 32u * in.at(r.e0) - 1u;   // LDS bit of position 128 v0
     const uint32_t* src = S + (bit >> 5);
+    const int32_t last = min(pt.n, int32_t(128u * (pt.v0 + P.len)) - 1);        // the part's last position
     hm::PartSyndrome syn;
     uint32_t x[NW][4];
 #pragma unroll
     for (uint32_t u = 0; u < NW; ++u) {
-        if (u < P.len) {
+        if (u < r.len) {
             read_window(src + 4u * u, bit, x[u]);
-            const int32_t top = pt.n - int32_t(128u * (pt.v0 + u));     // last position of the segment
+            const int32_t top = last - int32_t(128u * (pt.v0 + u));
             if (top < 127) hm::mask_window(x[u], top);
             if (u == 0) x[0][0] &= pt.v0 == 0 ? ~1u : ~0u;              // there is no position 0
             syn.add(x[u], pt.v0 + u);
@@ -700,10 +707,13 @@ __device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r,
     wave_sync();
     out.clear(5u, S, lane);
     wave_sync();
+    // v0 anew: v0 + u would be held for every window from the first loop on
+    uint32_t v0 = pt.v0;
+    asm volatile("" : "+v"(v0));
 #pragma unroll
     for (uint32_t u = 0; u < NW; ++u) {
         if (u < pt.cnt) {
-            const uint32_t v = pt.v0 + u;
+            const uint32_t v = v0 + u;
             uint32_t at = pt.K + hm::run_base(v);
             if (u == 0 && v == 0) {
                 hm::compact_head(x[0]);
@@ -750,8 +760,8 @@ __device__ __forceinline__ void encode_parts(const SegArgs& a, const WaveRun& r)
     const hm::Parts& P = r.P;
     uint32_t* S = r.W;
     uint32_t* X = r.X + slot * GROUP;
-    const Run in(r.msg, (64 / GROUP - 1) * r.ms + r.mw), out(r.enc, (64 / GROUP - 1) * r.es + r.ew);
-    const uint32_t mb = in.at(slot * r.ms), eb = out.at(slot * r.es);
+    const Run in(r.msg, r.mruns), out(r.enc, r.eruns);
+    const uint32_t mb = in.at(r.m0), eb = out.at(r.e0);
     X[gl] = 0;
     if (a.cached)
         in.load<false>(r.msg, S, lane);
@@ -817,11 +827,15 @@ constexpr uint32_t kSegXcdChunk = 8;
 constexpr uint32_t kPartMinBytes = 192;
 
 // 256 / GROUP packets per block, GROUP <= 64 lanes each.  A wave takes the part
-// form when all its packets are there, have one shape of at least kPartMinBytes
-// whose parts fit NW windows, and lie at one stride in either arena, their runs inside the arenas
-// and inside the wave's LDS; the window form otherwise.
+// form when all its packets are there, have at least kPartMinBytes and parts
+// that fit NW windows, and lie end to end in both arenas or, being of one
+// shape, at one stride in either, their runs inside the arenas and inside the
+// wave's LDS; the window form otherwise.  NW = 8 fits the 72 registers that let
+// 7 waves share a SIMD; without the bound the compiler takes 78 (800-byte
+// packets 166 against 160 us).
 template <uint32_t GROUP, uint32_t NW, uint32_t BATCH, bool DECODE>
-__global__ __launch_bounds__(64 * kSegWaves) void seg_parts_kernel(SegArgs a)
+__global__ __launch_bounds__(64 * kSegWaves) __attribute__((amdgpu_waves_per_eu(NW == 8 ? 7 : 1)))
+void seg_parts_kernel(SegArgs a)
 {
     constexpr uint32_t PACKETS = 64 / GROUP;                     // of a wave
     extern __shared__ uint64_t lds[];
@@ -853,17 +867,58 @@ __global__ __launch_bounds__(64 * kSegWaves) void seg_parts_kernel(SegArgs a)
             alike = alike && (!a.syndromes || (d.seg_off <= a.syndrome_count && t <= a.syndrome_count - d.seg_off));
         const uint32_t most = (wave_dwords - kPartRunExtra) / 2u;                      // words of a run in LDS
         const bool apart = r.es >= r.ew && r.ms >= r.mw && r.es <= most && r.ms <= most;
-        const uint32_t eruns = (PACKETS - 1) * r.es + r.ew, mruns = (PACKETS - 1) * r.ms + r.mw;
-        if (r.P.len <= NW && apart && eruns <= most && mruns <= most && e0 <= a.enc_words &&
-            eruns <= a.enc_words - e0 && m0 <= a.msg_words && mruns <= a.msg_words - m0 &&
+        r.eruns = (PACKETS - 1) * r.es + r.ew;
+        r.mruns = (PACKETS - 1) * r.ms + r.mw;
+        if (r.P.len <= NW && apart && r.eruns <= most && r.mruns <= most && e0 <= a.enc_words &&
+            r.eruns <= a.enc_words - e0 && m0 <= a.msg_words && r.mruns <= a.msg_words - m0 &&
             __ballot(alike) == ~uint64_t(0)) {
             r.enc = const_cast<uint64_t*>(a.enc) + e0;
             r.msg = a.msg + m0;
+            r.e0 = slot * r.es;
+            r.m0 = slot * r.ms;
+            r.len = r.P.len;
             if constexpr (DECODE)
                 decode_parts<GROUP, NW>(a, r, pk, d.seg_off);
             else
                 encode_parts<GROUP, NW>(a, r);
             return;
+        }
+    }
+    if (PACKETS > 1 && !one_shape) {
+        // packets of several shapes, end to end
+        const uint32_t most = (wave_dwords - kPartRunExtra) / 2u;
+        const uint64_t e0 = readfirstlane64(d.enc_word_off), m0 = readfirstlane64(d.msg_word_off);
+        bool ok = d.t <= GROUP && d.msg_bytes >= kPartMinBytes &&
+                  make_layout(d.msg_bytes, d.t, a.max_msg_bytes, r.Lo);
+        if constexpr (DECODE)
+            ok = ok && (!a.syndromes || (d.seg_off <= a.syndrome_count && d.t <= a.syndrome_count - d.seg_off));
+        if (__ballot(ok) == ~uint64_t(0)) {
+            r.P = hm::make_parts(d.t, r.Lo.rem ? r.Lo.vA : r.Lo.vB, GROUP);
+            const uint32_t ew = (r.Lo.total + 63u) / 64u, mw = (d.msg_bytes + 7u) / 8u;
+            r.eruns = r.mruns = r.len = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < PACKETS; ++k) {
+                if (slot == k) {
+                    r.e0 = r.eruns;
+                    r.m0 = r.mruns;
+                }
+                r.eruns += __builtin_amdgcn_readlane(ew, k * GROUP);
+                r.mruns += __builtin_amdgcn_readlane(mw, k * GROUP);
+                r.len = max(r.len, uint32_t(__builtin_amdgcn_readlane(r.P.len, k * GROUP)));
+            }
+            const bool in_line = d.enc_word_off == e0 + r.e0 && d.msg_word_off == m0 + r.m0;
+            if (r.len <= NW && r.eruns <= most && r.mruns <= most && e0 <= a.enc_words &&
+                r.eruns <= a.enc_words - e0 && m0 <= a.msg_words && r.mruns <= a.msg_words - m0 &&
+                __ballot(in_line) == ~uint64_t(0)) {
+                r.enc = const_cast<uint64_t*>(a.enc) + e0;
+                r.msg = a.msg + m0;
+                r.ew = r.es = r.mw = r.ms = 0;
+                if constexpr (DECODE)
+                    decode_parts<GROUP, NW>(a, r, pk, d.seg_off);
+                else
+                    encode_parts<GROUP, NW>(a, r);
+                return;
+            }
         }
     }
     if constexpr (GROUP == 64) {

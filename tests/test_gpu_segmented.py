@@ -485,3 +485,63 @@ def test_segmented_automatic_group_edges(gpu_device, P, msg_bytes):
     torch.cuda.synchronize()
     want = oracle.seg_encode_many(msgs, t, row_bytes=8 * ew)
     assert np.array_equal(enc_t.cpu().numpy().view(np.uint8).reshape(P, 8 * ew), want)
+
+
+@pytest.mark.parametrize("seg_mode", [8, 16, 32, 64], indirect=True)
+@pytest.mark.parametrize("lo,hi,t_lo,t_hi,slip", [(192, 640, 1, 8, None), (192, 1280, 2, 7, None),
+                                                  (180, 700, 1, 8, None), (300, 2000, 2, 6, None),
+                                                  (500, 4096, 1, 16, None), (192, 640, 1, 8, 21)])
+def test_segmented_packets_of_several_shapes_end_to_end(gpu_device, seg_mode, lo, hi, t_lo, t_hi, slip):
+    """Packets of several shapes end to end from an odd first word, some
+    waves with a packet too short, of too many segments or (slip) a word
+    further on than the end of the one before; both directions against the
+    oracle, and nothing beside the packets is written."""
+    import torch
+
+    P = 70
+    rng = np.random.default_rng(lo + hi + t_hi)
+    M, T = rng.integers(lo, hi + 1, P), rng.integers(t_lo, t_hi + 1, P)
+    M[8:16], T[8:16] = M[8], T[8]                   # a wave of one shape among them
+    seed = synth.workload_seed("gpu-seg-shapes", lo, hi)
+    d = np.zeros(P, dtype=hm.seg_packet_dtype())
+    e, m, s = 3, 1, 0
+    rows = []
+    for p in range(P):
+        mb, t = int(M[p]), int(T[p])
+        ew, mw = (oracle.seg_layout(mb, t)[3] + 63) // 64, (mb + 7) // 8
+        e, m = e + (p == slip), m + (p == slip)
+        d[p]["enc_word_off"], d[p]["msg_word_off"], d[p]["seg_off"], d[p]["msg_bytes"], d[p]["t"] = e, m, s, mb, t
+        sent = synth.packet_bytes(seed + p, 1, mb)
+        code = oracle.seg_encode_many(sent, t, row_bytes=8 * ew)
+        got = _received(seed + 1000 + p, 1, mb, t, 8 * ew, 0.4, 0.2)
+        rows.append((e, m, s, ew, mw, mb, t, sent, code, got))
+        e, m, s = e + ew, m + mw, s + t
+
+    def arena(words, parts):
+        a = np.full(words, 0x3C3C3C3C3C3C3C3C, dtype=np.uint64)
+        for first, count, data in parts:
+            row = np.zeros(8 * count, dtype=np.uint8)
+            row[:data.size] = data.reshape(-1)
+            a[first:first + count] = row.view(np.uint64)
+        return a
+
+    def on_device(a):
+        return torch.from_numpy(a.view(np.int64)).to(gpu_device)
+
+    desc = torch.from_numpy(d.view(np.uint8)).to(gpu_device)
+    ref = [oracle.seg_decode_many(r[9], r[5], r[6]) for r in rows]
+    enc_t, msg_t = on_device(arena(e + 2, [(r[0], r[3], r[9]) for r in rows])), on_device(arena(m + 2, []))
+    syn = torch.zeros(s, dtype=torch.int16, device=gpu_device)
+    st = torch.zeros(P, dtype=torch.uint8, device=gpu_device)
+    hm.hamming_decode_segmented(enc_t, enc_t.numel(), desc, P, hi, msg_t, msg_t.numel(), syn, syn.numel(), st)
+    torch.cuda.synchronize()
+    want = arena(m + 2, [(r[1], r[4], f[0]) for r, f in zip(rows, ref)])
+    assert np.array_equal(msg_t.cpu().numpy().view(np.uint64), want)
+    assert np.array_equal(syn.cpu().numpy().view(np.uint16), np.concatenate([f[1].reshape(-1) for f in ref]))
+    assert np.array_equal(st.cpu().numpy(), np.concatenate([f[2].reshape(-1) for f in ref]))
+
+    msg_t, enc_t = on_device(arena(m + 2, [(r[1], r[4], r[7]) for r in rows])), on_device(arena(e + 2, []))
+    hm.hamming_encode_segmented(msg_t, msg_t.numel(), desc, P, hi, enc_t, enc_t.numel())
+    torch.cuda.synchronize()
+    want = arena(e + 2, [(r[0], r[3], r[8]) for r in rows])
+    assert np.array_equal(enc_t.cpu().numpy().view(np.uint64), want)
