@@ -23,7 +23,7 @@ struct EncShape {
     static constexpr int PER = C::WPC == 1 ? 2 : 1;                        // codewords per vector
     static constexpr uint32_t VPT = 2;                                     // vectors per thread (staged)
     // Vectors per thread of the direct kernel, loaded before the first is built.
-    // The 64 messages of a wave are 256 (r = 3) to 416 bytes (r = 5), so with
+    // The 128 messages of a wave's vectors are 64 (r = 3) or 176 bytes long, so with
     // one vector in flight a stream that is not in the Infinity Cache came at
     // less than 1 TB/s (r = 4, 2^26 codewords: 126 us against 107 with four, 90
     // against 85 where it is; eight: 110, 95).  r = 3 gains nothing (82 us).
@@ -74,7 +74,7 @@ __device__ __forceinline__ void store_vector(const uint32_t (&a)[EncShape<R>::PE
     }
 }
 
-// ---- short messages (r = 3..5): each thread loads its own stream words -----
+// ---- short messages (r = 3, 4): each thread loads its own stream words -----
 template <int R>
 __global__ __launch_bounds__(256) void encode_plain_kernel(const uint32_t* __restrict__ stream,
                                                            uint64_t stream_dwords, uint64_t n_cw,
@@ -109,16 +109,18 @@ __global__ __launch_bounds__(256) void encode_plain_kernel(const uint32_t* __res
     }
 }
 
-// ---- long messages (r = 6, 7, large r = 5): the stream is staged in LDS ------------
+// ---- long messages (r = 5..7): the stream is staged in LDS -----------------
 // A workgroup of 256 threads encodes one tile of 512 output vectors (two per
 // thread, 256 apart, so stores stay coalesced).  The tile's slice of the
 // message stream is staged in LDS with coalesced 64-bit loads; each thread
 // then funnel-shifts its messages out of LDS instead of issuing PW+1 32-bit
-// loads per codeword at a k-bit stride.  A workgroup loops over tiles and
+// loads per codeword at a k-bit stride (r = 5 from HBM, 2^24 codewords 33 against
+// 41 us, 2^25 62 against 78; in the caches 28 and 54 either way; 2^21 5.3
+// against 6.3; r = 4 no difference).  A workgroup loops over tiles and
 // loads the next tile's words into registers while it encodes the current
 // one.  Words past the end of the stream are staged as zero (their bits are
 // masked off or belong to no codeword).
-template <int R>
+template <int R, bool NT>
 __global__ __launch_bounds__(256) void encode_staged_kernel(const uint64_t* __restrict__ stream, uint64_t stream_q,
                                                             uint64_t n_cw, uint64_t* __restrict__ cw_out)
 {
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(256) void encode_staged_kernel(const uint64_t* __re
         for (uint32_t l = 0; l < LPT; ++l) {
             const uint32_t e = threadIdx.x + 256u * l;
             const uint64_t q = q0 + e;
-            nxt[l] = (e < S::LDS_Q && q < stream_q) ? __builtin_nontemporal_load(stream + q) : uint64_t(0);
+            nxt[l] = (e < S::LDS_Q && q < stream_q) ? (NT ? __builtin_nontemporal_load(stream + q) : stream[q]) : uint64_t(0);
         }
     };
     uint64_t t = blockIdx.x;
@@ -178,28 +180,30 @@ __global__ __launch_bounds__(256) void encode_staged_kernel(const uint64_t* __re
 constexpr uint64_t kEncodeMaxBlocks = 32768;
 constexpr uint64_t kEncodeDirectMaxBlocks = 65536;
 
-// Message streams of r = 5 above this are staged too.  The direct kernel reads
-// through the caches and is faster where the stream is in the Infinity Cache
-// (2^26 codewords, 208 MiB: 105 against 120 us; 2^25: 54 against 61), the staged
-// one is the same either way (2^26, not cached: 120 against 153 us; 2^25: 61
-// against 78); beyond half of the 256 MB the stream is rarely there.
-constexpr uint64_t kEncodeCachedBytes = uint64_t(128) << 20;
+// Message streams of r = 6 and 7 up to this are read with ordinary loads, longer
+// ones with nontemporal loads.  The 256 MB Infinity Cache can still hold what
+// was written or read shortly before: r = 6, 2^21 codewords 5.7-6.5 against 7.6
+// us (8 against 6.5 from HBM too), 2^22 9.6 against 12; r = 7, 2^22 19.5 against
+// 22 (from HBM 23.1 against 22.8).  Beyond, ordinary loads lose: r = 6, 2^26 173
+// against 161 us.  The shorter streams of r = 5 win with them at every size
+// (2^26, 208 MiB: 119 against 121 us from HBM, 108 against 120 repeated).
+constexpr uint64_t kEncodeCachedBytes = uint64_t(64) << 20;
 
 template <int R>
 static hipError_t launch_encode_r(const void* stream_in, uint64_t n_cw, uint64_t* out, hipStream_t stream)
 {
     using C = Code<R>;
     const uint64_t stream_q = (n_cw * C::K + 63) / 64;
-    if (R >= 6 || (R == 5 && stream_q * 8 > kEncodeCachedBytes)) {
-        if constexpr (R >= 5) {
-            using T = EncShape<R>;
-            uint64_t blocks = (n_cw + T::CW - 1) / T::CW;
-            if (blocks > kEncodeMaxBlocks) blocks = kEncodeMaxBlocks;
-            if (blocks == 0) return hipSuccess;
-            hipLaunchKernelGGL((encode_staged_kernel<R>), dim3(uint32_t(blocks)), dim3(256), 0, stream,
-                               static_cast<const uint64_t*>(stream_in), stream_q, n_cw, out);
-        }
-    } else if constexpr (R <= 5) {
+    if constexpr (R >= 5) {
+        using T = EncShape<R>;
+        uint64_t blocks = (n_cw + T::CW - 1) / T::CW;
+        if (blocks > kEncodeMaxBlocks) blocks = kEncodeMaxBlocks;
+        if (blocks == 0) return hipSuccess;
+        void (*const kernel)(const uint64_t*, uint64_t, uint64_t, uint64_t*) =
+            R >= 6 && stream_q * 8 > kEncodeCachedBytes ? encode_staged_kernel<R, true> : encode_staged_kernel<R, false>;
+        hipLaunchKernelGGL(kernel, dim3(uint32_t(blocks)), dim3(256), 0, stream,
+                           static_cast<const uint64_t*>(stream_in), stream_q, n_cw, out);
+    } else {
         constexpr uint64_t per = EncShape<R>::PER;
         constexpr uint64_t per_block = 256 * EncShape<R>::DIRECT;
         uint64_t blocks = ((n_cw + per - 1) / per + per_block - 1) / per_block;

@@ -347,8 +347,8 @@ def test_encode_parity_odd_output_word_around_blocks(gpu_device, r, n_cw):
 
 @pytest.mark.parametrize("n_cw", [41297762, 41297763])
 def test_encode_large_hamming_31_26_either_form(gpu_device, n_cw):
-    """A message stream of exactly 128 MiB (read directly) and one just above
-    (staged) against the two halves encoded on their own."""
+    """A message stream of exactly 128 MiB and one just above against the two
+    halves encoded on their own."""
     import torch
 
     stream = synth.message_stream_torch(synth.workload_seed("gpu-enc-large", 5), n_cw, 5, gpu_device)
@@ -359,6 +359,31 @@ def test_encode_large_hamming_31_26_either_form(gpu_device, n_cw):
     b = hm.encode(stream[half * 26 // 64:].clone(), n_cw - half, 5)
     torch.cuda.synchronize()
     assert torch.equal(whole[:half], a) and torch.equal(whole[half:], b)
+
+
+@pytest.mark.parametrize("r", [6, 7])
+@pytest.mark.parametrize("over", [0, 1])
+def test_encode_either_side_of_the_cached_size(gpu_device, r, over):
+    """A message stream of 64 MiB (read through the caches) and one just above
+    (nontemporal): both halves encoded on their own give the same codewords,
+    and the last ones equal the oracle's."""
+    import torch
+
+    wpc, k = hm.words_per_codeword(r), hm.hamming_message_bits(r)
+    n = (64 << 23) // k + over
+    stream = synth.message_stream_torch(synth.workload_seed("gpu-enc-cached", r), n, r, gpu_device)
+    assert (stream.numel() * 8 > 64 << 20) == bool(over)
+    whole = hm.encode(stream, n, r)
+    half = n // 2 // 64 * 64
+    tail = stream[half * k // 64:].clone()
+    a, b = hm.encode(stream, half, r), hm.encode(tail, n - half, r)
+    torch.cuda.synchronize()
+    assert torch.equal(whole[:half * wpc], a) and torch.equal(whole[half * wpc:], b)
+    last = (n - half) // 64 * 64 - 64
+    m = n - half - last
+    words = tail[last * k // 64:].cpu().numpy().view(np.uint64)
+    want = oracle.encode(words, m, r).reshape(-1)
+    assert np.array_equal(b[last * wpc:].cpu().numpy().view(np.uint64).reshape(-1), want)
 
 
 @pytest.mark.parametrize("r", [3, 6, 7])
