@@ -403,7 +403,7 @@ int hamming_decode_segmented(const uint64_t *enc_arena, uint64_t enc_words, cons
  * (no effect on results): the threads that cooperate on one packet, 8, 16 or 32 (part of a wave), 64 (a
  * wave) or 256 (a workgroup).  0 lets the library choose: a workgroup per
  * packet for batches of at most 2048 packets (latency), else a group sized to
- * max_msg_bytes (throughput).  Process-wide.  Returns HAMMING_OK or
+ * max_msg_bytes and the number of packets (throughput).  Process-wide.  Returns HAMMING_OK or
  * HAMMING_EINVAL. */
 int hamming_seg_config_set(uint32_t threads_per_packet);
 int hamming_seg_config_get(uint32_t *threads_per_packet);
