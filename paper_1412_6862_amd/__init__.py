@@ -182,8 +182,13 @@ def _current_stream() -> int:
 
 
 def _message_stream_bytes(n_cw: int, r: int) -> int:
-    """``hamming_data_bytes`` for the size of a tensor, without a foreign call."""
-    return (n_cw * ((1 << r) - 1 - r) + 63) // 64 * 8 if 3 <= r <= 7 else 0
+    """``hamming_data_bytes``, the bytes that the library writes, without a
+    foreign call where plain integers in range allow it.  Other integer types
+    go through the library: numpy's would wrap at their own width, and the
+    tensor would be shorter than what is written to it."""
+    if type(n_cw) is int and type(r) is int and 3 <= r <= 7 and 0 <= n_cw <= HAMMING_MAX_CODEWORDS:
+        return (n_cw * ((1 << r) - 1 - r) + 63) // 64 * 8
+    return hamming_data_bytes(n_cw, r)
 
 
 def _ptr(t) -> int:

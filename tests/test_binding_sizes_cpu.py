@@ -1,0 +1,24 @@
+"""Output sizes in the Python binding: the tensor that ``decode``,
+``decode_planes`` and ``Server.result`` size for a call has exactly the bytes
+that the library writes (``hamming_data_bytes``), for every integer type that
+the entry points take and past the ends of their ranges."""
+import numpy as np
+import pytest
+
+import paper_1412_6862_amd as hm
+
+COUNTS = [0, 1, 63, 64, 1000, 80_000_000, hm.HAMMING_MAX_CODEWORDS, hm.HAMMING_MAX_CODEWORDS + 1, 1 << 60,
+          (1 << 64) + 5, -1]
+
+
+@pytest.mark.parametrize("kind", [int, np.int8, np.uint8, np.int32, np.uint32, np.int64, np.uint64])
+def test_message_stream_bytes_is_what_the_library_writes(kind):
+    for r in (2, 3, 4, 5, 6, 7, 8):
+        for n in COUNTS:
+            want = hm.hamming_data_bytes(n, r)
+            assert hm._message_stream_bytes(n, kind(r)) == want, (n, r)
+            if kind is not int and not np.iinfo(kind).min <= n <= np.iinfo(kind).max:
+                continue
+            got = hm._message_stream_bytes(kind(n), r)
+            assert got == want and type(got) is int, (n, r)
+            assert hm._message_stream_bytes(kind(n), kind(r)) == want, (n, r)
