@@ -11,6 +11,7 @@ operation has a CPU fallback.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import threading
@@ -207,6 +208,16 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
+def _on_stream(stream, device):
+    """Context in which torch's own kernels go to the stream of a call."""
+    import torch
+
+    if stream is None:
+        return contextlib.nullcontext()
+    s = _stream(stream)
+    return torch.cuda.stream(torch.cuda.ExternalStream(s, device=device) if s else torch.cuda.default_stream(device))
+
+
 # ---- C entry points, same names ------------------------------------------------
 
 def hamming_message_bits(r: int) -> int:
@@ -349,7 +360,8 @@ def to_planes(codewords, r: int, stream=None):
     pw = (n_cw + 63) // 64
     planes = torch.empty(((1 << r) - 1) * pw, dtype=torch.int64, device=cw.device)
     if (n_cw + 31) // 32 % 2:       # the converter writes half of each plane's last word
-        planes.view(-1, pw)[:, -1].zero_()
+        with _on_stream(stream, cw.device):
+            planes.view(-1, pw)[:, -1].zero_()
     hamming_to_planes(cw, n_cw, r, planes, pw, stream)
     return planes, pw
 

@@ -137,3 +137,35 @@ def test_planes_full_size_equals_plain_decode_and_oracle_samples(gpu_device, r, 
         d_ref, e_ref = oracle.decode(y, r)
         got = d[first * k // 8:first * k // 8 + d_ref.size].cpu().numpy()
         assert np.array_equal(got, d_ref) and np.array_equal(e[first:first + 64].cpu().numpy(), e_ref)
+
+
+@pytest.mark.parametrize("r,n_cw", [(3, 2049), (6, 33 * 32 - 5), (7, 1)])
+@pytest.mark.parametrize("how", ["stream", "pointer", "null"])
+def test_to_planes_on_a_stream_of_its_own_is_whole_when_that_stream_is_done(gpu_device, r, n_cw, how):
+    """An odd count of 32 codewords leaves half of each plane's last word to a
+    clear, which belongs to the stream that the call names: with torch's current
+    stream still busy, and recycled memory that holds other bits, the planes are
+    complete once the named stream is."""
+    import torch
+
+    assert (n_cw + 31) // 32 % 2
+    y = received_words(synth.workload_seed("gpu-to-planes-stream", r, n_cw), n_cw, r, p_single=0.3)
+    want = to_planes(y, n_cw, r)
+    cw = to_device(y, gpu_device)
+    current, other = torch.cuda.Stream(), torch.cuda.Stream()
+    stream = {"stream": other, "pointer": other.cuda_stream, "null": 0}[how]
+    waited = torch.cuda.default_stream() if how == "null" else other
+    torch.cuda.synchronize()
+    with torch.cuda.stream(current):
+        old = torch.full((want.size,), 0x5A5A5A5A5A5A5A5A, dtype=torch.int64, device=gpu_device)
+        del old
+        current.synchronize()
+        torch.cuda._sleep(2000000)
+        planes, pw = hm.to_planes(cw, r, stream=stream)
+        assert torch.cuda.current_stream() == current
+    waited.synchronize()
+    with torch.cuda.stream(waited):
+        first = planes.cpu().numpy().view(np.uint64).reshape(want.shape)
+    torch.cuda.synchronize()
+    last = planes.cpu().numpy().view(np.uint64).reshape(want.shape)
+    assert pw == want.shape[1] and np.array_equal(first, want) and np.array_equal(last, want)
