@@ -28,6 +28,8 @@ struct BatchWs {
 struct BatchArgs {
     const uint64_t* cw_arena;
     uint64_t cw_words;
+    uint64_t in_bytes;       // input bytes of the largest batch the arguments allow
+    uint64_t blocks;         // workgroups of one chunk per wave that it fills (the grid before a cap)
     const hamming_packet* descs;
     const uint32_t* n_packets_dev;
     uint32_t max_packets;
@@ -88,9 +90,6 @@ constexpr uint64_t kWavesPerBlockHost = 4;
 
 hipError_t launch_batch(const BatchArgs& a, int schedule, uint32_t grid, hipStream_t stream);
 
-// Whether launch_batch decodes this batch in one or two launches.
-bool batch_is_short(const BatchArgs& a, uint32_t grid);
-
 // Validate the arguments of hamming_decode_batch, lay the caller's workspace
 // out and size the decode grid.  Returns a status code; *out and *grid are
 // set on HAMMING_OK.
@@ -110,7 +109,7 @@ constexpr uint32_t kMaxChunkLog2 = 6;
 // A batch small enough to travel in the kernel arguments: its descriptors
 // and the exclusive prefix sum of their tile counts, computed on the host by
 // a caller that has validated the descriptors itself (the server).  One
-// launch then replaces the descriptor copy, the plan and the two map kernels.
+// launch then replaces the descriptor copy, the plan and the maps.
 constexpr uint32_t kSmallBatchMax = 16;
 struct SmallBatch {
     const uint64_t* cw_arena;
@@ -126,7 +125,7 @@ struct SmallBatch {
 // descriptors itself (the server): the exclusive prefix sum of the packets'
 // tile counts, a coarse tile-to-packet map (entry j = the packet holding tile
 // j << coarse_log2) and the descriptors, uploaded in one copy.  One launch of
-// decode_planned_batch_kernel then replaces the plan and map kernels: a wave
+// decode_planned_batch_kernel then replaces the plan and its maps: a wave
 // reads its map entry and probes the prefix sums 64 entries at a time from
 // there.  The map has at most about two entries per packet, so the probe
 // almost always ends in its first step.

@@ -157,6 +157,7 @@ int batch_prepare(const uint64_t* cw_arena, uint64_t cw_words, const hamming_pac
     memset(&a, 0, sizeof a);
     a.cw_arena = cw_arena;
     a.cw_words = cw_words;
+    a.in_bytes = batch_input_bytes(cw_words, max_codewords);
     a.descs = descs;
     a.n_packets_dev = n_packets_dev;
     a.max_packets = max_packets;
@@ -177,6 +178,7 @@ int batch_prepare(const uint64_t* cw_arena, uint64_t cw_words, const hamming_pac
     const uint64_t blocks =
         batch_grid_blocks(cw_words, max_packets, max_codewords, g_grid_cap.load(), a.chunk_log2, schedule);
     *grid = uint32_t(blocks);
+    a.blocks = batch_grid_blocks(cw_words, max_packets, max_codewords, 0, a.chunk_log2, schedule);
     // the fine map has at most one entry per chunk of the bound, and a block of
     // its kernel fills 1024 (it loops, so this only sizes its grid)
     const uint64_t chunks =
@@ -280,7 +282,7 @@ int hamming_decode_batch(const uint64_t* cw_arena, uint64_t cw_words, const hamm
     if (rc != HAMMING_OK) return rc;
     // one or two launches are cheaper than a graph of them (own stream: 48 short
     // packets 6 us direct against 15-16 us, 1000 packets of 47 MB 19 against 24)
-    if (hm::batch_is_short(a, grid))
+    if (hm::batch_form(a.max_packets, a.blocks) != hm::BatchForm::three)
         return hm::launch_batch(a, schedule, grid, stream) == hipSuccess ? HAMMING_OK : HAMMING_EDEVICE;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return HAMMING_EDEVICE;

@@ -51,23 +51,6 @@ struct Schedule {
                   "invalid lane width");
 };
 
-// How a batch is launched (launch_batch_s), by the packets and the grid that the
-// caller's arguments allow.  A launch after another costs 4-5 us (the gap and
-// the ramp), so short batches take fewer:
-//  * one launch, every workgroup planning for itself, up to kOnePackets packets
-//    and kOneBlocks workgroups (the planning, about 2 us, is paid once per
-//    resident workgroup: 200 packets, 34 MB: 14 us against 16 us with two
-//    launches and 21 with four; 256 packets, 140 MB: 41 against 35);
-//  * two, plan with a coarse map and decode, up to kMapPackets packets and
-//    kMapBlocks workgroups (1000 packets, 47 MB: 19.5 against 24 us), above
-//    which the decode's longer lookup outweighs a launch (2000 packets, 3.7 GB:
-//    decode 618-655 against 584-631 us with the fine map);
-//  * three, plan, fine map and decode.
-constexpr uint32_t kOnePackets = 256;
-constexpr uint32_t kOneBlocks = 4096;
-constexpr uint32_t kMapPackets = 1024;
-constexpr uint32_t kMapBlocks = 16384;
-
 using Sched0 = Schedule<8, 8, 8, 8, 2, 4>;
 using Sched1 = Schedule<8, 4, 4, 4, 2, 5>;
 using Sched2 = Schedule<8, 8, 8, 4, 2, 5>;
@@ -373,7 +356,7 @@ struct LdsStarts {
 // the whole batch for itself (a descriptor per thread, the prefix sums in LDS)
 // and then decodes its chunks as decode_batch_kernel does; the first one also
 // writes the statuses and the totals.
-template <class S>
+template <class S, bool NT>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(S::waves_per_simd)))
 void decode_batch_one_kernel(BatchArgs a, const hamming_packet* __restrict__ descs)
 {
@@ -405,8 +388,8 @@ void decode_batch_one_kernel(BatchArgs a, const hamming_packet* __restrict__ des
         const uint64_t t = c << cl;
         const uint32_t p = probe_packet(starts, n, t, 0);
         const uint64_t t_end = (t + (uint64_t(1) << cl) < total) ? t + (uint64_t(1) << cl) : total;
-        decode_span<S, false>(t, t_end, __builtin_amdgcn_readfirstlane(p), LdsStarts{starts}, descs, a.cw_arena, a.data_arena,
-                       a.errpos_arena, lds);
+        decode_span<S, NT>(t, t_end, __builtin_amdgcn_readfirstlane(p), LdsStarts{starts}, descs, a.cw_arena,
+                           a.data_arena, a.errpos_arena, lds);
     }
 }
 
@@ -520,28 +503,22 @@ hipError_t launch_planned_batch(const PlannedBatch& b, int schedule, hipStream_t
     }
 }
 
-static bool one_launch(const BatchArgs& a, uint32_t grid) { return a.max_packets <= kOnePackets && grid <= kOneBlocks; }
-static bool two_launches(const BatchArgs& a, uint32_t grid) { return a.max_packets <= kMapPackets && grid <= kMapBlocks; }
-
-bool batch_is_short(const BatchArgs& a, uint32_t grid) { return one_launch(a, grid) || two_launches(a, grid); }
-
 template <class S>
 static hipError_t launch_batch_s(const BatchArgs& a, uint32_t grid, hipStream_t stream)
 {
-    if (one_launch(a, grid)) {
-        hipLaunchKernelGGL((decode_batch_one_kernel<S>), dim3(grid), dim3(kBlockThreads), 0, stream, a, a.descs);
+    const BatchForm form = batch_form(a.max_packets, a.blocks);
+    if (form == BatchForm::one) {
+        void (*const kernel)(BatchArgs, const hamming_packet*) =
+            batch_reads_cached(a.in_bytes) ? decode_batch_one_kernel<S, false> : decode_batch_one_kernel<S, true>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlockThreads), 0, stream, a, a.descs);
         return hipGetLastError();
     }
-    if (two_launches(a, grid)) {
+    if (form == BatchForm::two) {
         hipLaunchKernelGGL((batch_plan_map_kernel<S>), dim3(1), dim3(1024), 0, stream, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        // Up to as many blocks as the one-launch form takes the packets are read
-        // through the caches, which hold them (measured warm, against streaming
-        // loads: 600 packets, 27 MB, 14.4 against 15.0 us; 1000 packets, 47 MB,
-        // 18.4 against 19.3, 83 MB 24.1 against 25.2); beyond, as any large batch.
         void (*const kernel)(BatchArgs, const BatchWs*, const uint32_t*, const uint64_t*, const hamming_packet*) =
-            grid <= kOneBlocks ? decode_mapped_batch_kernel<S, false> : decode_mapped_batch_kernel<S, true>;
+            batch_reads_cached(a.in_bytes) ? decode_mapped_batch_kernel<S, false> : decode_mapped_batch_kernel<S, true>;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlockThreads), 0, stream, a, a.ws, a.coarse, a.tile_start,
                            a.descs);
         return hipGetLastError();
