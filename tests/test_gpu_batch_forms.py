@@ -1,8 +1,10 @@
 """The launch forms of the batched decode (one, two or three launches): which
-one a call takes.  Outputs are compared with the oracle
+one a call takes, and the three-launch form's own branches, with max_packets
+above 1024 so that short batches reach it.  Outputs are compared with the oracle
 byte for byte; the form is read off the workspace, of which each form writes
 different parts (the prefix sums in the two- and three-launch forms, the coarse
 map in the two-launch form, the fine map in the three-launch form)."""
+import numpy as np
 import pytest
 
 import paper_1412_6862_amd as hm
@@ -11,6 +13,7 @@ from test_gpu_batch import _build_batch, _check_outputs, _expect, _to_dev
 pytestmark = pytest.mark.gpu
 
 FORMS = {(False, False, False): "one", (True, True, False): "two", (True, False, True): "three"}
+MAX = 1100                       # above the packets of the one- and two-launch forms
 
 
 def _poison(bd):
@@ -79,3 +82,78 @@ def test_batch_form_and_loads_either_side_of_their_bounds(gpu_device, config, ma
     _decode(bd)
     assert _form(bd) == form
     _check_outputs(bd, descs, _expect(ys, descs), data_fill=0x77, ep_fill=0x88)
+
+
+@pytest.mark.parametrize("chunk_log2,fine_log2", [(0, 1), (0, 3), (0, 6), (2, 3), (3, 6), (1, 1)])
+@pytest.mark.parametrize("schedule", [0, 1, 2, 3])
+@pytest.mark.parametrize("use_graph", [0, 1])
+def test_three_launches_grouped_fine_map(gpu_device, config, chunk_log2, fine_log2, schedule, use_graph):
+    """A fine map of 2^fine_log2 tiles per entry, sized from the batch's tile
+    count: where an entry spans several chunks every wave probes from it."""
+    arena, descs, ys = _build_batch(1300 + fine_log2 + 7 * schedule + 50 * chunk_log2, 60)
+    expect = _expect(ys, descs)
+    config(schedule=schedule, use_graph=use_graph, chunk_log2=chunk_log2)
+    cw = _to_dev(arena, gpu_device)
+    full = hm.BatchDecoder(cw, MAX)
+    full.set_packets(descs)
+    _decode(full)
+    tiles = full.totals()["tiles"]
+    assert _form(full) == "three" and full.totals()["fine_log2"] == chunk_log2 and tiles >= 1 << fine_log2
+    _check_outputs(full, descs, expect, data_fill=0x77, ep_fill=0x88)
+    entries = (tiles >> fine_log2) + 1
+    bd = hm.BatchDecoder(cw, MAX, workspace_bytes=hm.hamming_batch_workspace_min_bytes(MAX) - 4 + 4 * entries)
+    bd.set_packets(descs)
+    _decode(bd)
+    assert _form(bd) == "three" and bd.totals()["fine_log2"] == fine_log2 and bd.totals()["tiles"] == tiles
+    _check_outputs(bd, descs, expect, data_fill=0x77, ep_fill=0x88)
+
+
+@pytest.mark.parametrize("schedule", [0, 1, 2, 3])
+@pytest.mark.parametrize("grid_cap", [0, 3])
+@pytest.mark.parametrize("one_entry", [0, 1])
+def test_three_launches_many_tiny_and_empty_packets(gpu_device, config, schedule, grid_cap, one_entry):
+    """1100 tiny and empty packets, with a whole fine map and with a single
+    entry, from which every wave probes through runs of packets without tiles."""
+    rng = np.random.default_rng(1400 + schedule)
+    sizes = [int(rng.choice([0, 0, 1, 5, 64, 127, 128, 129, 300])) for _ in range(MAX)]
+    rs = [int(rng.integers(3, 8)) for _ in range(MAX)]
+    arena, descs, ys = _build_batch(1500 + schedule, MAX, sizes=sizes, rs=rs)
+    config(schedule=schedule, grid_cap=grid_cap, chunk_log2=0)
+    bd = hm.BatchDecoder(_to_dev(arena, gpu_device), MAX,
+                         workspace_bytes=hm.hamming_batch_workspace_min_bytes(MAX) if one_entry else None)
+    bd.set_packets(descs)
+    _decode(bd)
+    t = bd.totals()
+    assert _form(bd) == "three" and t["tiles"] > 64 and t["packets"] == MAX
+    assert ((t["tiles"] >> t["fine_log2"]) == 0) == bool(one_entry)
+    assert not bd.status.cpu().numpy().any()
+    _check_outputs(bd, descs, _expect(ys, descs), data_fill=0x77, ep_fill=0x88)
+
+
+@pytest.mark.parametrize("one_entry", [0, 1])
+def test_three_launches_graph_serves_changing_counts(gpu_device, config, one_entry):
+    """One graph, several packet counts read on the device (none among them),
+    with eager work between the replays; then the same arguments without one."""
+    import torch
+
+    arena, descs, ys = _build_batch(1600 + one_entry, 30)
+    expect = _expect(ys, descs)
+    bd = hm.BatchDecoder(_to_dev(arena, gpu_device), MAX,
+                         workspace_bytes=hm.hamming_batch_workspace_min_bytes(MAX) if one_entry else None)
+    bd.set_packets(descs)
+    s = torch.cuda.Stream()
+    for use_graph, counts in ((1, (30, 7, 0, 19, 30, 1)), (0, (30, 0, 5))):
+        config(use_graph=use_graph, chunk_log2=0)
+        for n in counts:
+            bd.data.fill_(0x3333333333333333)
+            bd.errpos.fill_(0x44)
+            bd.n_dev.fill_(n)
+            _poison(bd)
+            s.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(s):
+                bd.decode(stream=s)
+            torch.cuda.synchronize()
+            assert bd.totals()["packets"] == n
+            if bd.totals()["tiles"]:
+                assert _form(bd) == "three"
+            _check_outputs(bd, descs[:n], expect[:n], data_fill=0x33, ep_fill=0x44)
