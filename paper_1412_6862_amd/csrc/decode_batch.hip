@@ -408,8 +408,8 @@ void decode_small_batch_kernel(SmallBatch b)
     uint32_t p = 0;
     while (p + 1 < b.n && b.tile_start[p + 1] <= t) ++p;    // packets without tiles are passed over
     const hamming_packet d = b.descs[p];
-    decode_any_run<S, false>(d, t - b.tile_start[p], t + 1 - b.tile_start[p], b.cw_arena, b.data_arena, b.errpos_arena,
-                      lds);
+    decode_any_run<S, true>(d, t - b.tile_start[p], t + 1 - b.tile_start[p], b.cw_arena, b.data_arena, b.errpos_arena,
+                            lds);
 }
 
 // Last packet p with tile_start[p] <= t, given tile_start[lo] <= t < tile_start[n]

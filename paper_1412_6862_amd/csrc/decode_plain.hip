@@ -13,7 +13,7 @@ namespace hm {
 // per wave when the grid covers the packet); a grid smaller than the packet
 // keeps two tiles of loads in flight per wave and pays its set-up once for
 // many tiles.
-template <int R, int U, bool NT>
+template <int R, int U>
 __global__ __launch_bounds__(kBlockThreads) void decode_plain_kernel(
     const uint64_t* __restrict__ cw, uint64_t n_cw, uint64_t* __restrict__ data, uint64_t data_words,
     uint8_t* __restrict__ errpos, uint64_t n_tiles, uint32_t flags, uint32_t xcd_chunk)
@@ -24,21 +24,18 @@ __global__ __launch_bounds__(kBlockThreads) void decode_plain_kernel(
     uint32_t* lds = reinterpret_cast<uint32_t*>(&lds_raw[wave][0]);
     const uint64_t waves = uint64_t(gridDim.x) * kWavesPerBlock;
     const uint64_t t = uint64_t(xcd_block(blockIdx.x, gridDim.x, xcd_chunk)) * kWavesPerBlock + wave;
-    decode_run<R, U, NT>(cw, n_cw, t, n_tiles, waves, data, data_words, errpos, lds, flags);
+    decode_run<R, U, true>(cw, n_cw, t, n_tiles, waves, data, data_words, errpos, lds, flags);
 }
 
 // ---- launchers ----------------------------------------------------------------
 
-// Packets of at most this many input bytes are read with ordinary loads, larger
-// ones with nontemporal loads.  Received words are usually decoded soon after
-// they arrive, and up to a quarter of the 256 MB Infinity Cache they are still
-// there: three buffers in turn, r = 6, 2^22 codewords (32 MiB) 11.2 against 13.8
-// us and 2^23 20.7 against 24.5; r = 7, 2^22 19.9 against 25.3; r = 4, 2^23 14.5
-// against 17.0.  When they are not, ordinary loads cost 0-8% (r = 6, 2^22 16.3
-// against 15.9 us, 2^23 26.4 against 25.1; r = 3, 2^23 15.7 against 14.5).  From
-// 128 MiB on they are slower either way (r = 6, 2^24: 47.6 against 43.9 us, 2^26
-// 182 against 160).
-constexpr uint64_t kDecodeCachedBytes = uint64_t(64) << 20;
+// Every packet is read with streaming (nontemporal) loads.  Ordinary loads win only
+// where the same buffer is decoded over and over out of the Infinity Cache (r = 6,
+// 32 MiB 9.9 against 12.2 us).  Words that were just written, which a decoder
+// usually gets, come faster with streaming loads: r = 6, 32 MiB after a copy 10.7
+// against 11.6 us, after a kernel that wrote them 9.2 against 10.4, after a transfer
+// from the host 17.4 against 17.9; r = 3, 63 MiB 11.6 against 13.1 after a copy; from
+// HBM 14.0 against 15.5.  Up to 8 MiB there is no difference.
 
 template <int R, int U>
 static hipError_t launch_decode_ru(const DecodeLaunch& L, hipStream_t stream)
@@ -50,10 +47,8 @@ static hipError_t launch_decode_ru(const DecodeLaunch& L, hipStream_t stream)
     if (blocks == 0) return hipSuccess;
     uint32_t flags = 0;
     if (L.errpos && (reinterpret_cast<uintptr_t>(L.errpos) % U) == 0) flags |= kFlagEpVec;
-    const bool cached = L.n_cw * Code<R>::WPC * 8 <= kDecodeCachedBytes;
-    void (*const kernel)(const uint64_t*, uint64_t, uint64_t*, uint64_t, uint8_t*, uint64_t, uint32_t, uint32_t) =
-        cached ? decode_plain_kernel<R, U, false> : decode_plain_kernel<R, U, true>;
-    hipLaunchKernelGGL(kernel, dim3(uint32_t(blocks)), dim3(kBlockThreads), 0, stream, L.cw, L.n_cw, L.data, L.data_words, L.errpos, n_tiles, flags, L.xcd_chunk);
+    hipLaunchKernelGGL((decode_plain_kernel<R, U>), dim3(uint32_t(blocks)), dim3(kBlockThreads), 0, stream,
+                       L.cw, L.n_cw, L.data, L.data_words, L.errpos, n_tiles, flags, L.xcd_chunk);
     return hipGetLastError();
 }
 
