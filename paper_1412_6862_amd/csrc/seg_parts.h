@@ -137,6 +137,31 @@ __host__ __device__ inline void expand_head(uint32_t (&m)[4])
     m[3] = (m2 >> 24) | (m3 << 8);
 }
 
+// A staged run lies in LDS in blocks of 32 dwords, each followed by room for four
+// more: while packets are read these hold the first four dwords of the next block,
+// and while results are built they collect what is ORed past a block's end, which
+// is merged into the next block at last.  The five dwords of a window are thus
+// consecutive wherever it starts, and lanes whose windows lie a multiple of 32
+// dwords apart, as those of segments and packets of about 1024 bits or a multiple
+// do, meet 4 dwords apart in the banks instead of all in one.
+constexpr uint32_t kBlockDwords = 32, kBlockRoom = 4;
+
+// LDS dword of dword a of the run's area; with R < kBlockRoom, dword a is also at
+// block_at(a) - kBlockRoom if a % kBlockDwords == R (the room of the block before).
+__host__ __device__ inline uint32_t block_at(uint32_t a) { return a + a / kBlockDwords * kBlockRoom; }
+
+// LDS dwords of an area of `dwords` dwords, the last block's room included.
+__host__ __device__ constexpr uint32_t block_area(uint32_t dwords)
+{
+    return dwords + (dwords + kBlockDwords - 1u) / kBlockDwords * kBlockRoom;
+}
+
+// Dwords of the largest area that `lds` LDS dwords hold: block_area(it) <= lds.
+__host__ __device__ constexpr uint32_t block_capacity(uint32_t lds)
+{
+    return lds < kBlockRoom ? 0u : (lds - kBlockRoom) * kBlockDwords / (kBlockDwords + kBlockRoom);
+}
+
 // A window to be placed at bit `at` (>= 0) of a dword array: the window's bits
 // go to dwords first .. first + 4, where first may be -1 (that dword then gets
 // zero bits only).

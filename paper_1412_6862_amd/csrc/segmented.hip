@@ -32,9 +32,14 @@
 #include "seg_parts.h"
 #include "tile.h"
 
+using hm::block_area;
+using hm::block_at;
+using hm::block_capacity;
 using hm::funnel128;
 using hm::head_expand;
 using hm::head_message;
+using hm::kBlockDwords;
+using hm::kBlockRoom;
 using hm::mask_top;
 using hm::run_start;
 using hm::small_div;
@@ -348,6 +353,7 @@ struct SegArgs {
     uint8_t* status;
     uint32_t slice_words;      // per-packet LDS buffer of the window form (accumulators excluded)
     uint32_t slot_dwords;      // LDS dwords per packet of the part form's kernels
+    uint32_t run_words;        // words of the longest run that a wave of them can stage
     uint32_t cached;           // read packets with ordinary (1) or nontemporal (0) loads
 };
 
@@ -507,21 +513,30 @@ __device__ __forceinline__ void encode_packet(const SegArgs& a, const hamming_se
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr uint32_t kPartLoads = 8;          // 16-byte loads a lane has in flight while a run is staged
-constexpr uint32_t kPartPad = 4;            // dwords in front of the run in LDS
-
-// LDS dwords of a wave beside its run: the pad, the run's shift within a line,
-// what is cleared and ORed in after it, and one syndrome per lane.  Lanes past
-// their segment's last window read up to 43 + 4 NW dwords past the run's start
-// and words, which the syndromes cover.
-constexpr uint32_t kPartRunExtra = kPartPad + 30u + 8u + 64u;
 constexpr uint32_t kPartStores = 4;         // 16-byte vectors it reads back before it stores the first
+constexpr uint32_t kPartPad = 4;            // dwords in front of the run
+
+// The wave's LDS: the run's area (the pad, the run's shift within a line, the run,
+// what is cleared and ORed in after it) in blocks, then one syndrome per lane, then
+// kPartSlack dwords.  Lanes past their segment's last window read up to 39 + 4 NW
+// dwords past the pad and the run's words, which the syndromes and the slack cover.
+constexpr uint32_t kPartEnds = kPartPad + 30u + 8u;
+constexpr uint32_t kPartSlack = 12u;
+
+// LDS dword of area dword a; BLOCKS: the area lies in blocks (seg_parts.h).
+template <bool BLOCKS>
+__device__ __forceinline__ uint32_t place(uint32_t a)
+{
+    return BLOCKS ? block_at(a) : a;
+}
 
 // A run of consecutive 64-bit words that a wave moves between global memory
 // and LDS in 16-byte vectors, lane 0 starting on a 128-byte line: word w of
-// the run sits at LDS dword kPartPad + 2 (shift + w), vector j holds words
-// 2j - shift and 2j + 1 - shift, and vectors lo .. hi - 1 lie in the run
+// the run is dword kPartPad + 2 (shift + w) of its area,
+// vector j holds words 2j - shift and 2j + 1 - shift, and vectors lo .. hi - 1 lie in the run
 // altogether.  The first and the last word may lie in no whole vector; they
 // are moved alone, so no access leaves the run.
+template <bool BLOCKS>
 struct Run {
     uint32_t words, shift, lo, hi;
 
@@ -529,8 +544,17 @@ struct Run {
         : words(words_), shift(uint32_t(reinterpret_cast<uintptr_t>(first_word) >> 3) & 15u),
           lo((shift + 1u) / 2u), hi((shift + words) / 2u) {}
 
-    // LDS dword of word w.
+    // Area dword of word w, and LDS place of vector j.
     __device__ uint32_t at(uint32_t w) const { return kPartPad + 2u * (shift + w); }
+
+    static __device__ u32x4* vector(uint32_t* S, uint32_t j)
+    {
+        return reinterpret_cast<u32x4*>(S + place<BLOCKS>(kPartPad + 4u * j));
+    }
+    static __device__ const u32x4* vector(const uint32_t* S, uint32_t j)
+    {
+        return reinterpret_cast<const u32x4*>(S + place<BLOCKS>(kPartPad + 4u * j));
+    }
 
     template <bool NT>
     __device__ __forceinline__ void load(const uint64_t* src, uint32_t* S, uint32_t lane) const
@@ -553,17 +577,40 @@ struct Run {
             }
 #pragma unroll
             for (uint32_t u = 0; u < kPartLoads; ++u)
-                if (base + u * 64 < hi) *reinterpret_cast<u32x4*>(S + kPartPad + 4u * j[u]) = x[u];
+                if (base + u * 64 < hi) {
+                    u32x4* const to = vector(S, j[u]);
+                    *to = x[u];
+                    if (BLOCKS && (kPartPad / 4u + j[u]) % (kBlockDwords / 4u) == 0) to[-1] = x[u];
+                }
         }
-        if (lane < 2)
-            *reinterpret_cast<uint2*>(S + at(edge)) = make_uint2(uint32_t(edge_word), uint32_t(edge_word >> 32));
+        if (lane < 2) {
+            uint2* const to = reinterpret_cast<uint2*>(S + place<BLOCKS>(at(edge)));
+            const uint2 y = make_uint2(uint32_t(edge_word), uint32_t(edge_word >> 32));
+            *to = y;
+            if (BLOCKS && at(edge) % kBlockDwords < kBlockRoom) to[-int(kBlockRoom / 2)] = y;
+        }
     }
 
-    // Clears the run's dwords in LDS and at least `more` dwords after them.
+    // Clears the run's dwords in LDS and at least `more` dwords after them, the
+    // blocks' rooms included.
     __device__ __forceinline__ void clear(uint32_t more, uint32_t* S, uint32_t lane) const
     {
-        for (uint32_t j = lane; 4u * j < 2u * (shift + words) + more; j += 64)
-            *reinterpret_cast<u32x4*>(S + kPartPad + 4u * j) = u32x4{0u, 0u, 0u, 0u};
+        const uint32_t last = place<BLOCKS>(kPartPad + 2u * (shift + words) + more - 1u);
+        for (uint32_t j = kPartPad / 4u + lane; 4u * j <= last; j += 64)
+            reinterpret_cast<u32x4*>(S)[j] = u32x4{0u, 0u, 0u, 0u};
+    }
+
+    // Blocks only: merges the rooms into the blocks after them.  Others may set or flip bits of
+    // the run at the same time: no two of these touch one bit.
+    __device__ __forceinline__ void merge(uint32_t* S, uint32_t lane) const
+    {
+        if constexpr (!BLOCKS) return;
+        constexpr uint32_t STEP = kBlockDwords + kBlockRoom;
+        for (uint32_t b = lane + 1u; b * kBlockDwords < kPartPad + 2u * (shift + words); b += 64) {
+            const u32x4 x = *reinterpret_cast<const u32x4*>(S + b * STEP - kBlockRoom);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) atomicXor(S + b * STEP + k, x[k]);
+        }
     }
 
     // Stores the run.  Of every `stride` words of it `packet` are a packet's and
@@ -573,7 +620,7 @@ struct Run {
     {
         if (packet != stride) {
             for (uint32_t j = lane; j < (shift + words + 1u) / 2u; j += 64) {
-                const u32x4 x = *reinterpret_cast<const u32x4*>(S + kPartPad + 4u * j);
+                const u32x4 x = *vector(S, j);
                 const int32_t w = int32_t(2u * j) - int32_t(shift);                  // the vector's first word
                 const uint32_t in0 = w < 0 ? packet : uint32_t(w) - small_div(uint32_t(w), stride) * stride;
                 const uint32_t in1 = w + 1 < 0 ? packet : w < 0 || in0 + 1u == stride ? 0u : in0 + 1u;
@@ -593,7 +640,7 @@ struct Run {
 #pragma unroll
             for (uint32_t u = 0; u < kPartStores; ++u) {
                 if (base + u * 64 >= hi) continue;
-                x[u] = *reinterpret_cast<const u32x4*>(S + kPartPad + 4u * min(base + u * 64 + lane, hi - 1u));
+                x[u] = *vector(S, min(base + u * 64 + lane, hi - 1u));
             }
 #pragma unroll
             for (uint32_t u = 0; u < kPartStores; ++u) {
@@ -603,7 +650,7 @@ struct Run {
         }
         if (lane < 2 && ((lane == 0 ? shift : shift + words) & 1u)) {
             const uint32_t w = lane == 0 ? 0u : words - 1u;
-            const uint2 y = *reinterpret_cast<const uint2*>(S + at(w));
+            const uint2 y = *reinterpret_cast<const uint2*>(S + place<BLOCKS>(at(w)));
             __builtin_nontemporal_store(uint64_t(y.x) | (uint64_t(y.y) << 32), dst + w);
         }
     }
@@ -635,9 +682,11 @@ struct Part {
     }
 };
 
-// Window of five dwords at LDS dword p, bit sh (0..31): four dwords.
-__device__ __forceinline__ void read_window(const uint32_t* p, uint32_t sh, uint32_t (&x)[4])
+// Window of five dwords from area dword a, bit sh (mod 32), on: four dwords.
+template <bool BLOCKS>
+__device__ __forceinline__ void read_window(const uint32_t* S, uint32_t a, uint32_t sh, uint32_t (&x)[4])
 {
+    const uint32_t* p = S + place<BLOCKS>(a);
     const u32x4 w = *reinterpret_cast<const u32x4a4*>(p);
     const uint32_t e = p[4];
     x[0] = hm::align32(w.y, w.x, sh);
@@ -646,10 +695,13 @@ __device__ __forceinline__ void read_window(const uint32_t* p, uint32_t sh, uint
     x[3] = hm::align32(e, w.w, sh);
 }
 
-__device__ __forceinline__ void or_window(uint32_t* p, const hm::Placed& w)
+// ORs a placed window in, its dword 0 being area dword a.
+template <bool BLOCKS>
+__device__ __forceinline__ void or_window(uint32_t* S, uint32_t a, const hm::Placed& w)
 {
+    uint32_t* p = S + place<BLOCKS>(a + uint32_t(w.first));
 #pragma unroll
-    for (int k = 0; k < 5; ++k) atomicOr(p + w.first + k, w.y[k]);
+    for (int k = 0; k < 5; ++k) atomicOr(p + k, w.y[k]);
 }
 
 // The packets of a wave: this lane's packet's layout, parts and first word in
@@ -666,10 +718,37 @@ struct WaveRun {
     uint32_t *W, *X;
 };
 
+// Whether equal packets lie so that about half of their parts or more begin in the
+// banks of the first one, in either run: segments, parts and packets a multiple of
+// 16 dwords (512 bits) apart, all of them.  Lanes step through their parts together,
+// so such lanes wait for each other at every access, and the wave stages its runs
+// in blocks instead.  2^18 packets, decode and encode: 633 bytes, t = 5 (every lane
+// in one bank) 151 and 156 -> 73 and 75 us; 2^17: 1908 bytes, t = 5 193 and 202 -> 88
+// and 87, 1020 bytes, t = 2 (half of the lanes) 81 and 82 -> 45 and 48, 384 bytes,
+// t = 2 27 and 26 -> 22 and 24.  Blocks cost an address per window, a second store
+// per block and the merge, so other shapes do without: they would take 3-15% longer,
+// and steps of 28 dwords would meet in one bank (1600 bytes, t = 2 73 against 133
+// us).  In scalar instructions, most waves leaving after the first two: counting
+// the lanes with ballots cost every other shape 1-4%.
+__device__ __forceinline__ bool lanes_collide(const WaveRun& r)
+{
+    // t - 1 steps of `bits` stay within the 3 dwords before or after a multiple of m
+    const auto near = [&](uint32_t bits, uint32_t m) {
+        const int32_t d = int32_t((bits + m / 2u) % m) - int32_t(m / 2u);
+        return uint32_t(d < 0 ? -d : d) * (r.Lo.t - 1u) <= 112u;
+    };
+    const auto side = [&](uint32_t words, uint32_t bits) {
+        if (words % 8u) return false;
+        if (r.P.parts == 1 || r.len % 4u == 0) return near(bits, 512u);
+        return r.P.parts == 2 && words % 16u == 0 && near(bits, 1024u);
+    };
+    return side(r.es, r.Lo.nA) || side(r.ms, r.Lo.q);
+}
+
 // Decodes the wave's packets with GROUP lanes each, every lane its part.  The
 // messages are built over the received words once every lane holds its
 // windows in registers.
-template <uint32_t GROUP, uint32_t NW>
+template <uint32_t GROUP, uint32_t NW, bool BLOCKS>
 __device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r, uint64_t pk, uint64_t seg_off)
 {
     const uint32_t lane = threadIdx.x & 63u, gl = lane % GROUP, slot = lane / GROUP;
@@ -677,25 +756,24 @@ __device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r,
     const hm::Parts& P = r.P;
     uint32_t* S = r.W;
     uint32_t* X = r.X + slot * GROUP;
-    const Run in(r.enc, r.eruns), out(r.msg, r.mruns);
+    const Run<BLOCKS> in(r.enc, r.eruns), out(r.msg, r.mruns);
     const uint32_t mb = out.at(r.m0);
     X[gl] = 0;
     if (a.cached)
-        in.load<false>(r.enc, S, lane);
+        in.template load<false>(r.enc, S, lane);
     else
-        in.load<true>(r.enc, S, lane);
+        in.template load<true>(r.enc, S, lane);
     wave_sync();
 
     const Part pt(Lo, P, gl);
-    const uint32_t bit = pt.o + 128u * pt.v0 + 32u * in.at(r.e0) - 1u;   // LDS bit of position 128 v0
-    const uint32_t* src = S + (bit >> 5);
+    const uint32_t bit = pt.o + 128u * pt.v0 + 32u * in.at(r.e0) - 1u;   // area bit of position 128 v0
     const int32_t last = min(pt.n, int32_t(128u * (pt.v0 + P.len)) - 1);        // the part's last position
     hm::PartSyndrome syn;
     uint32_t x[NW][4];
 #pragma unroll
     for (uint32_t u = 0; u < NW; ++u) {
         if (u < r.len) {
-            read_window(src + 4u * u, bit, x[u]);
+            read_window<BLOCKS>(S, (bit >> 5) + 4u * u, bit, x[u]);
             const int32_t top = last - int32_t(128u * (pt.v0 + u));
             if (top < 127) hm::mask_window(x[u], top);
             if (u == 0) x[0][0] &= pt.v0 == 0 ? ~1u : ~0u;              // there is no position 0
@@ -721,20 +799,21 @@ __device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r,
             } else {
                 x[u][0] &= ~hm::is_pow2_window(v);
             }
-            or_window(S + mb, hm::place_window(x[u], at));
+            or_window<BLOCKS>(S, mb, hm::place_window(x[u], at));
         }
     }
     wave_sync();
 
     // checksum owners: lane gl has segment gl; an error at a message position
     // flips that message bit, one at a checksum position changes none
+    out.merge(S, lane);
     uint32_t st = 0;
     if (gl < Lo.t) {
         const uint32_t s = X[gl], n = Lo.n(gl);
         if (s >= 1 && s <= n) {
             if (s & (s - 1u)) {
                 const uint32_t b = Lo.K(gl) + s - (31u - __clz(s)) - 2u;
-                atomicXor(&S[mb + (b >> 5)], 1u << (b & 31u));
+                atomicXor(&S[place<BLOCKS>(mb + (b >> 5))], 1u << (b & 31u));
             }
             st = 1;
         } else if (s > n) {
@@ -752,7 +831,7 @@ __device__ __forceinline__ void decode_parts(const SegArgs& a, const WaveRun& r,
 
 // Encodes the wave's packets: the same parts, each window built from its run
 // of message bits and placed into the encoded packet.
-template <uint32_t GROUP, uint32_t NW>
+template <uint32_t GROUP, uint32_t NW, bool BLOCKS>
 __device__ __forceinline__ void encode_parts(const SegArgs& a, const WaveRun& r)
 {
     const uint32_t lane = threadIdx.x & 63u, gl = lane % GROUP, slot = lane / GROUP;
@@ -760,13 +839,13 @@ __device__ __forceinline__ void encode_parts(const SegArgs& a, const WaveRun& r)
     const hm::Parts& P = r.P;
     uint32_t* S = r.W;
     uint32_t* X = r.X + slot * GROUP;
-    const Run in(r.msg, r.mruns), out(r.enc, r.eruns);
+    const Run<BLOCKS> in(r.msg, r.mruns), out(r.enc, r.eruns);
     const uint32_t mb = in.at(r.m0), eb = out.at(r.e0);
     X[gl] = 0;
     if (a.cached)
-        in.load<false>(r.msg, S, lane);
+        in.template load<false>(r.msg, S, lane);
     else
-        in.load<true>(r.msg, S, lane);
+        in.template load<true>(r.msg, S, lane);
     wave_sync();
 
     const Part pt(Lo, P, gl);
@@ -778,7 +857,7 @@ __device__ __forceinline__ void encode_parts(const SegArgs& a, const WaveRun& r)
             const uint32_t v = pt.v0 + u;
             const bool head = u == 0 && v == 0;
             const uint32_t at = pt.K + (head ? 0u : hm::run_base(v));
-            read_window(S + mb + (at >> 5), at, x[u]);
+            read_window<BLOCKS>(S, mb + (at >> 5), at, x[u]);
             if (head)
                 hm::expand_head(x[u]);
             else
@@ -796,20 +875,21 @@ __device__ __forceinline__ void encode_parts(const SegArgs& a, const WaveRun& r)
 #pragma unroll
     for (uint32_t u = 0; u < NW; ++u) {
         // one dword further on, so that the stream bit is never negative
-        if (u < pt.cnt) or_window(S + eb - 1, hm::place_window(x[u], pt.o + 128u * (pt.v0 + u) + 31u));
+        if (u < pt.cnt) or_window<BLOCKS>(S, eb - 1u, hm::place_window(x[u], pt.o + 128u * (pt.v0 + u) + 31u));
     }
     wave_sync();
 
     // checksum position 2^j of segment gl takes bit j of the syndrome of its
     // message bits, which makes the segment's syndrome 0
+    out.merge(S, lane);
     if (gl < Lo.t) {
         const uint32_t s = X[gl], o = Lo.o(gl);
         const uint32_t w = (s & 3u) | ((s & 4u) << 1) | ((s & 8u) << 4) | ((s & 16u) << 11) | ((s & 32u) << 26);
-        atomicOr(&S[eb + (o >> 5)], w << (o & 31u));
-        atomicOr(&S[eb + (o >> 5) + 1u], (w >> 1) >> (31u - (o & 31u)));
+        atomicOr(&S[place<BLOCKS>(eb + (o >> 5))], w << (o & 31u));
+        atomicOr(&S[place<BLOCKS>(eb + (o >> 5) + 1u)], (w >> 1) >> (31u - (o & 31u)));
         for (uint32_t j = 6; (s >> j) != 0; ++j) {
             const uint32_t b = o + (1u << j) - 1u;
-            if ((s >> j) & 1u) atomicOr(&S[eb + (b >> 5)], 1u << (b & 31u));
+            if ((s >> j) & 1u) atomicOr(&S[place<BLOCKS>(eb + (b >> 5))], 1u << (b & 31u));
         }
     }
     wave_sync();
@@ -846,7 +926,7 @@ void seg_parts_kernel(SegArgs a)
     WaveRun r;
     const uint32_t wave_dwords = PACKETS * a.slot_dwords;
     r.W = reinterpret_cast<uint32_t*>(lds) + wave * wave_dwords;
-    r.X = r.W + wave_dwords - 64u;
+    r.X = r.W + wave_dwords - kPartSlack - 64u;
     const hamming_seg_packet d = a.descs[pk];
     const uint32_t M = __builtin_amdgcn_readfirstlane(d.msg_bytes), t = __builtin_amdgcn_readfirstlane(d.t);
     // all 64 lanes are there, and their packets have one shape
@@ -865,7 +945,7 @@ void seg_parts_kernel(SegArgs a)
         bool alike = d.enc_word_off == e0 + uint64_t(slot) * r.es && d.msg_word_off == m0 + uint64_t(slot) * r.ms;
         if constexpr (DECODE)
             alike = alike && (!a.syndromes || (d.seg_off <= a.syndrome_count && t <= a.syndrome_count - d.seg_off));
-        const uint32_t most = (wave_dwords - kPartRunExtra) / 2u;                      // words of a run in LDS
+        const uint32_t most = a.run_words;
         const bool apart = r.es >= r.ew && r.ms >= r.mw && r.es <= most && r.ms <= most;
         r.eruns = (PACKETS - 1) * r.es + r.ew;
         r.mruns = (PACKETS - 1) * r.ms + r.mw;
@@ -877,10 +957,17 @@ void seg_parts_kernel(SegArgs a)
             r.e0 = slot * r.es;
             r.m0 = slot * r.ms;
             r.len = r.P.len;
+            if (PACKETS > 1 && lanes_collide(r)) {
+                if constexpr (DECODE)
+                    decode_parts<GROUP, NW, PACKETS != 1>(a, r, pk, d.seg_off);
+                else
+                    encode_parts<GROUP, NW, PACKETS != 1>(a, r);
+                return;
+            }
             if constexpr (DECODE)
-                decode_parts<GROUP, NW>(a, r, pk, d.seg_off);
+                decode_parts<GROUP, NW, false>(a, r, pk, d.seg_off);
             else
-                encode_parts<GROUP, NW>(a, r);
+                encode_parts<GROUP, NW, false>(a, r);
             return;
         }
     }
@@ -889,7 +976,7 @@ void seg_parts_kernel(SegArgs a)
         // they are not comes first: with gaps between them the wave takes the window
         // form, and the layout in front of that cost it 10% (2^18 packets of 400 to
         // 2000 bytes 189 us, 177 now, 171 in a kernel of the window form alone)
-        const uint32_t most = (wave_dwords - kPartRunExtra) / 2u;
+        const uint32_t most = a.run_words;
         const uint32_t mw = (d.msg_bytes + 7u) / 8u, first = uint32_t(d.msg_word_off);
         const uint32_t before = __shfl_up(first + mw, GROUP);                          // the packet before ends here
         bool ok = d.t <= GROUP && d.msg_bytes >= kPartMinBytes && (slot == 0 || first == before);
@@ -919,9 +1006,9 @@ void seg_parts_kernel(SegArgs a)
                 r.msg = a.msg + m0;
                 r.ew = r.es = r.mw = r.ms = 0;
                 if constexpr (DECODE)
-                    decode_parts<GROUP, NW>(a, r, pk, d.seg_off);
+                    decode_parts<GROUP, NW, false>(a, r, pk, d.seg_off);
                 else
-                    encode_parts<GROUP, NW>(a, r);
+                    encode_parts<GROUP, NW, false>(a, r);
                 return;
             }
         }
@@ -979,14 +1066,16 @@ uint32_t auto_threads_per_packet(uint32_t n_packets, uint32_t max_msg_bytes, boo
     return max_msg_bytes <= 2048 ? 16u : (max_msg_bytes <= 3072 ? 32u : 64u);
 }
 
-// LDS dwords per packet of the part form's kernels (a wave has 64 / group): the
-// encoded words (at most 16 checksum bits for each of t <= group segments) and
-// the wave's share of kPartRunExtra; at least what the window form takes.
+// LDS dwords per packet of the part form's kernels (a wave has 64 / group): its
+// share of a wave whose packets are the largest (at most 16 checksum bits for each
+// of t <= group segments); at least what the window form takes.
 uint32_t part_slot_dwords(uint32_t max_msg_bytes, uint32_t group, uint32_t slice_words)
 {
     const uint32_t ew = (8u * max_msg_bytes + 16u * (group < HAMMING_SEG_MAX_T ? group : HAMMING_SEG_MAX_T) + 63u) / 64u;
     const uint32_t packets = 64u / group;
-    const uint32_t parts = 2u * ew + (kPartRunExtra + packets - 1u) / packets;
+    // block_capacity may lose up to four dwords of an area to its rounding
+    const uint32_t wave = block_area(2u * packets * ew + kPartEnds + 4u) + 64u + kPartSlack;
+    const uint32_t parts = (wave + packets - 1u) / packets;
     const uint32_t windows = group < 64 ? 2u * (slice_words + kAccWords) : 0u;
     return ((parts > windows ? parts : windows) + 3u) & ~3u;
 }
@@ -1040,6 +1129,7 @@ void launch(const SegArgs& a0, uint32_t n_packets, uint32_t max_msg_bytes, hipSt
                  : group == 32 ? part_kernel<32, DECODE>(max_msg_bytes)
                                : part_kernel<64, DECODE>(max_msg_bytes);
         a.slot_dwords = part_slot_dwords(max_msg_bytes, group, a.slice_words);
+        a.run_words = (block_capacity(64u / group * a.slot_dwords - kPartSlack - 64u) - kPartEnds) / 2u;
         lds = size_t(per_block) * a.slot_dwords * 4;
     }
     // one launch per slice of packets that fits a dispatch's 32-bit work-item
@@ -1113,7 +1203,7 @@ int hamming_decode_segmented(const uint64_t* enc_arena, uint64_t enc_words, cons
     if (rc != HAMMING_OK || n_packets == 0) return rc;
     if (syndromes && (reinterpret_cast<uintptr_t>(syndromes) & 1u)) return HAMMING_EALIGN;
     SegArgs a{enc_arena, enc_words, descs, n_packets, max_msg_bytes, msg_arena, msg_words,
-              syndromes, syndromes ? syndrome_count : 0, status, msg_slice_words(max_msg_bytes), 0, 0};
+              syndromes, syndromes ? syndrome_count : 0, status, msg_slice_words(max_msg_bytes), 0, 0, 0};
     launch<true>(a, n_packets, max_msg_bytes, stream);
     return hipGetLastError() == hipSuccess ? HAMMING_OK : HAMMING_EDEVICE;
 }
@@ -1125,7 +1215,7 @@ int hamming_encode_segmented(const uint64_t* msg_arena, uint64_t msg_words, cons
     int rc = check_common(enc_arena, descs, n_packets, msg_arena, max_msg_bytes);
     if (rc != HAMMING_OK || n_packets == 0) return rc;
     SegArgs a{enc_arena, enc_words, descs, n_packets, max_msg_bytes, const_cast<uint64_t*>(msg_arena), msg_words,
-              nullptr, 0, nullptr, enc_slice_words(max_msg_bytes), 0, 0};
+              nullptr, 0, nullptr, enc_slice_words(max_msg_bytes), 0, 0, 0};
     launch<false>(a, n_packets, max_msg_bytes, stream);
     return hipGetLastError() == hipSuccess ? HAMMING_OK : HAMMING_EDEVICE;
 }

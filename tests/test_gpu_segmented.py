@@ -545,3 +545,13 @@ def test_segmented_packets_of_several_shapes_end_to_end(gpu_device, seg_mode, lo
     torch.cuda.synchronize()
     want = arena(e + 2, [(r[0], r[3], r[8]) for r in rows])
     assert np.array_equal(enc_t.cpu().numpy().view(np.uint64), want)
+
+
+@pytest.mark.parametrize("seg_mode", [8, 16, 32, 64], indirect=True)
+@pytest.mark.parametrize("msg_bytes,t", [(384, 2), (504, 4), (630, 5), (633, 5), (634, 5), (1020, 4), (1908, 3),
+                                         (1908, 5), (2000, 9), (3060, 3)])
+@pytest.mark.parametrize("gap", [0, 5])
+def test_segmented_segments_a_multiple_of_the_banks_apart(gpu_device, seg_mode, msg_bytes, t, gap):
+    """Segments and packets of 1024 bits or a multiple, or nearly: their windows
+    start on the edges of the blocks in which the run is staged."""
+    test_segmented_equal_packets_at_a_stride(gpu_device, seg_mode, msg_bytes, t, gap)
