@@ -365,9 +365,12 @@ constexpr uint32_t kAccWords = HAMMING_SEG_MAX_T + HAMMING_SEG_MAX_T / 2;
 // is the packet's message buffer in LDS (at least mw + 3 words) and acc its
 // accumulators.  With GROUP < 64 several packets share a wave, so pk, the descriptor and the
 // layout are per-lane values and wave-wide ballots are masked to the group.
-// Every thread of a group takes the same branches at the barriers.
+// Every thread of a group takes the same branches at the barriers.  The descriptor
+// comes by value: by reference its fields were loaded where they are used, 13
+// loads with a wait each instead of two (2048 packets of 2000 bytes 7.3 against
+// 6.8 us).
 template <uint32_t GROUP, uint32_t BATCH>
-__device__ __forceinline__ void decode_packet(const SegArgs& a, const hamming_seg_packet& d, uint64_t pk, uint32_t gl,
+__device__ __forceinline__ void decode_packet(const SegArgs& a, hamming_seg_packet d, uint64_t pk, uint32_t gl,
                                               uint64_t* Mb, uint64_t* acc)
 {
     const uint32_t M = d.msg_bytes, t = d.t;
@@ -441,7 +444,7 @@ __device__ __forceinline__ void decode_packet(const SegArgs& a, const hamming_se
 // buffer in LDS (at least ew + 3 words, E[0] in front of the stream) and acc its
 // accumulators.  A descriptor this launch cannot take is skipped.
 template <uint32_t GROUP, uint32_t BATCH>
-__device__ __forceinline__ void encode_packet(const SegArgs& a, const hamming_seg_packet& d, uint32_t gl, uint64_t* E,
+__device__ __forceinline__ void encode_packet(const SegArgs& a, hamming_seg_packet d, uint32_t gl, uint64_t* E,
                                               uint64_t* acc)
 {
     const uint32_t M = d.msg_bytes, t = d.t;
@@ -1026,21 +1029,32 @@ void seg_parts_kernel(SegArgs a)
     }
 }
 
-// A workgroup per packet, the latency form.
+// The window form alone, 256 / GROUP packets per block: a workgroup per packet, the
+// latency form, and batches of packets too short for the part form, which would
+// only pay for its checks (2^18 packets of 128 bytes 31.7 against 30.5 us).  The
+// packet is a per-lane value for every GROUP: from blockIdx alone a workgroup's one
+// descriptor and its layout would go through the scalar unit, which takes longer
+// (1500 packets with gaps 6.45 against 6.2 us).
 template <uint32_t GROUP, uint32_t BATCH>
 __global__ __launch_bounds__(64 * kSegWaves) void seg_decode_kernel(SegArgs a)
 {
     extern __shared__ uint64_t lds[];
-    const uint64_t pk = blockIdx.x;
-    decode_packet<GROUP, BATCH>(a, a.descs[pk], pk, threadIdx.x, lds, lds + a.slice_words);
+    const uint32_t slot = threadIdx.x / GROUP;
+    const uint64_t pk = uint64_t(blockIdx.x) * (64 * kSegWaves / GROUP) + slot;
+    if (pk >= a.n_packets) return;
+    uint64_t* slice = lds + slot * (a.slice_words + kAccWords);
+    decode_packet<GROUP, BATCH>(a, a.descs[pk], pk, threadIdx.x % GROUP, slice, slice + a.slice_words);
 }
 
 template <uint32_t GROUP, uint32_t BATCH>
 __global__ __launch_bounds__(64 * kSegWaves) void seg_encode_kernel(SegArgs a)
 {
     extern __shared__ uint64_t lds[];
-    const uint64_t pk = blockIdx.x;
-    encode_packet<GROUP, BATCH>(a, a.descs[pk], threadIdx.x, lds, lds + a.slice_words);
+    const uint32_t slot = threadIdx.x / GROUP;
+    const uint64_t pk = uint64_t(blockIdx.x) * (64 * kSegWaves / GROUP) + slot;
+    if (pk >= a.n_packets) return;
+    uint64_t* slice = lds + slot * (a.slice_words + kAccWords);
+    encode_packet<GROUP, BATCH>(a, a.descs[pk], threadIdx.x % GROUP, slice, slice + a.slice_words);
 }
 
 // Threads per packet when the caller leaves the choice to the library: a
@@ -1097,6 +1111,17 @@ void (*part_kernel(uint32_t max_msg_bytes))(SegArgs)
     }
 }
 
+// The window form's kernel for GROUP threads per packet; two windows ahead, as short
+// packets and a workgroup's share have few.
+template <uint32_t GROUP, bool DECODE>
+constexpr void (*window_kernel())(SegArgs)
+{
+    if constexpr (DECODE)
+        return seg_decode_kernel<GROUP, 2>;
+    else
+        return seg_encode_kernel<GROUP, 2>;
+}
+
 // Batches of at most this many message bytes are read with ordinary loads,
 // larger ones with nontemporal loads.  Packets are usually decoded soon after
 // they were written, and half the 256 MB Infinity Cache can still hold them:
@@ -1117,12 +1142,12 @@ void launch(const SegArgs& a0, uint32_t n_packets, uint32_t max_msg_bytes, hipSt
     const uint32_t per_block = 64 * kSegWaves / group;
     void (*kernel)(SegArgs);
     size_t lds;
-    if (group == 256) {
-        if constexpr (DECODE)
-            kernel = seg_decode_kernel<256, 2>;
-        else
-            kernel = seg_encode_kernel<256, 2>;
-        lds = size_t(a.slice_words + kAccWords) * 8;
+    if (group == 256 || (group < 64 && max_msg_bytes < kPartMinBytes)) {
+        kernel = group == 8    ? window_kernel<8, DECODE>()
+                 : group == 16 ? window_kernel<16, DECODE>()
+                 : group == 32 ? window_kernel<32, DECODE>()
+                               : window_kernel<256, DECODE>();
+        lds = size_t(per_block) * (a.slice_words + kAccWords) * 8;
     } else {
         kernel = group == 8    ? part_kernel<8, DECODE>(max_msg_bytes)
                  : group == 16 ? part_kernel<16, DECODE>(max_msg_bytes)
