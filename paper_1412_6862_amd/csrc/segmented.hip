@@ -1095,8 +1095,13 @@ uint32_t part_slot_dwords(uint32_t max_msg_bytes, uint32_t group, uint32_t slice
 }
 
 // The kernel for GROUP lanes per packet, with registers for 8 (encoding 9: the
-// compiler then needs 65 registers, with 8 it takes 86) or 12 windows in a lane.  A lane's share is max_msg_bytes / (16 group) windows if all
-// lanes have one; the largest share of t <= 8 segments is about 1.5 times that.
+// compiler then needs 65 registers, with 8 it takes 86), 12 or 15 windows in a lane.
+// A lane's share is max_msg_bytes / (16 GROUP) windows if all lanes have one; the
+// largest share of t <= 8 segments is about 1.5 times that.  Decoding with 8 lanes,
+// t = 5 has nine windows from 634 bytes on (2^18 packets of 634 bytes 86 -> 76 us; the
+// other t 1-3% slower than with 8).  On 16 lanes t = 9 and 10 have more than 12 from
+// 1715 bytes on (2000 bytes, t = 10, decode 253 us in the window form, 180 with 15
+// windows, t = 9 229 and 180; t <= 6 0-1% slower than with 12).
 // The window form loads 2 windows ahead while a thread has about five of them
 // (unused slots of a last batch cost loads and walk steps), 4 above (more
 // loads in flight); measured on the Table 1 grid.
@@ -1106,7 +1111,9 @@ void (*part_kernel(uint32_t max_msg_bytes))(SegArgs)
     if constexpr (GROUP == 64) {
         return seg_parts_kernel<64, 6, 2, DECODE>;       // six are enough for every shape
     } else {
-        const bool wide = max_msg_bytes > 80u * GROUP;
+        const bool wide = max_msg_bytes > (GROUP == 8 && DECODE ? 633u : 80u * GROUP);
+        if constexpr (GROUP == 16)
+            if (max_msg_bytes > 1714u) return seg_parts_kernel<GROUP, 15, 4, DECODE>;
         return wide ? seg_parts_kernel<GROUP, 12, 4, DECODE> : seg_parts_kernel<GROUP, DECODE ? 8 : 9, 2, DECODE>;
     }
 }

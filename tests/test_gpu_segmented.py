@@ -555,3 +555,12 @@ def test_segmented_segments_a_multiple_of_the_banks_apart(gpu_device, seg_mode, 
     """Segments and packets of 1024 bits or a multiple, or nearly: their windows
     start on the edges of the blocks in which the run is staged."""
     test_segmented_equal_packets_at_a_stride(gpu_device, seg_mode, msg_bytes, t, gap)
+
+
+@pytest.mark.parametrize("seg_mode", [8, 16], indirect=True)
+@pytest.mark.parametrize("msg_bytes,t", [(633, 5), (634, 5), (640, 5), (641, 5), (1024, 6), (1715, 10), (2002, 9),
+                                         (2003, 9), (2048, 9)])
+def test_segmented_longest_parts(gpu_device, seg_mode, msg_bytes, t):
+    """Parts of 8 and 9, and of up to 15 windows, where the part form's kernels
+    have registers for one more or one less."""
+    test_segmented_equal_packets_at_a_stride(gpu_device, seg_mode, msg_bytes, t, 0)
