@@ -44,10 +44,13 @@ struct PlaneShape {
     static constexpr int WAVES = 4;                              // waves per block
     // Lanes whose messages are staged at once.  A lane produces K dwords; a
     // buffer for all 64 lanes costs 14.3 KB per wave at r = 6 and 30 KB at
-    // r = 7 and left 9 and 5 waves on a CU, so the long messages go out in
-    // rounds of 32 and 16 lanes through 7.1 and 7.5 KB (r = 6, 2^26 codewords:
-    // 195 -> 184 us, r = 7, 2^25: 219 -> 195 us, 5.8 and 5.5 TB/s).
-    static constexpr int LANES = R == 7 ? 16 : (R == 6 ? 32 : 64);
+    // r = 7 and left 9 and 5 waves on a CU, so the long messages go out in two
+    // rounds of 32 lanes (r = 6, 2^26 codewords: 195 -> 184 us; r = 7, 3.3e7: 279 ->
+    // 225 us).  At r = 7 the registers allow 8 waves on a CU, and so do 15 KB for
+    // each: four rounds of 16 lanes were no faster at any size (225 us) and made the
+    // smallest packets slower (2 MiB of planes 12.1 us against 10.6 with two rounds
+    // and 11.4 with one for all lanes).
+    static constexpr int LANES = R >= 6 ? 32 : 64;
     static constexpr int MSG_DW = LANES * K;
     static constexpr int EP_DW = 64 * 8;                          // errpos dwords per wave, staged first
     static constexpr int LDS_DW = MSG_DW > EP_DW ? MSG_DW : EP_DW;
