@@ -95,7 +95,8 @@ __global__ __launch_bounds__(256) void encode_plain_kernel(const uint32_t* __res
                 const uint64_t d = o >> 5;
                 sh[v][u] = uint32_t(o & 31u);
 #pragma unroll
-                for (int q = 0; q <= C::PW; ++q) raw[v][u][q] = stream[d + q < stream_dwords ? d + q : stream_dwords - 1];
+                for (int q = 0; q <= C::PW; ++q)
+                    raw[v][u][q] = stream[d + q < stream_dwords ? d + q : stream_dwords - 1];
             }
         }
 #pragma unroll
@@ -139,7 +140,8 @@ __global__ __launch_bounds__(256) void encode_staged_kernel(const uint64_t* __re
         for (uint32_t l = 0; l < LPT; ++l) {
             const uint32_t e = threadIdx.x + 256u * l;
             const uint64_t q = q0 + e;
-            nxt[l] = (e < S::LDS_Q && q < stream_q) ? (NT ? __builtin_nontemporal_load(stream + q) : stream[q]) : uint64_t(0);
+            nxt[l] = 0;
+            if (e < S::LDS_Q && q < stream_q) nxt[l] = NT ? __builtin_nontemporal_load(stream + q) : stream[q];
         }
     };
     uint64_t t = blockIdx.x;
@@ -182,11 +184,12 @@ constexpr uint64_t kEncodeDirectMaxBlocks = 65536;
 
 // Message streams of r = 6 and 7 up to this are read with ordinary loads, longer
 // ones with nontemporal loads.  The 256 MB Infinity Cache can still hold what
-// was written or read shortly before: r = 6, 2^21 codewords 5.7-6.5 against 7.6
-// us (8 against 6.5 from HBM too), 2^22 9.6 against 12; r = 7, 2^22 19.5 against
-// 22 (from HBM 23.1 against 22.8).  Beyond, ordinary loads lose: r = 6, 2^26 173
-// against 161 us.  The shorter streams of r = 5 win with them at every size
-// (2^26, 208 MiB: 119 against 121 us from HBM, 108 against 120 repeated).
+// was written or read shortly before: r = 6, 16 MiB of messages just written 7.3
+// against 8.3 us, repeated 6.0 against 7.9, from HBM 8.4 either way; 63 MiB 21.5
+// against 25.3, 22.0 against 23.9 and 25.4 against 25.3; r = 7, 63 MiB 19.9 against
+// 22.7, 20.0 against 22.7 and 23.8 against 23.5.  Beyond, ordinary loads lose: r = 6,
+// 2^26 codewords 173 against 161 us.  r = 5 wins with them at every size (200 MiB of
+// messages 109 against 124 us just written, 113 against 119 from HBM).
 constexpr uint64_t kEncodeCachedBytes = uint64_t(64) << 20;
 
 template <int R>
@@ -199,8 +202,9 @@ static hipError_t launch_encode_r(const void* stream_in, uint64_t n_cw, uint64_t
         uint64_t blocks = (n_cw + T::CW - 1) / T::CW;
         if (blocks > kEncodeMaxBlocks) blocks = kEncodeMaxBlocks;
         if (blocks == 0) return hipSuccess;
-        void (*const kernel)(const uint64_t*, uint64_t, uint64_t, uint64_t*) =
-            R >= 6 && stream_q * 8 > kEncodeCachedBytes ? encode_staged_kernel<R, true> : encode_staged_kernel<R, false>;
+        void (*kernel)(const uint64_t*, uint64_t, uint64_t, uint64_t*) = encode_staged_kernel<R, false>;
+        if constexpr (R >= 6)
+            if (stream_q * 8 > kEncodeCachedBytes) kernel = encode_staged_kernel<R, true>;
         hipLaunchKernelGGL(kernel, dim3(uint32_t(blocks)), dim3(256), 0, stream,
                            static_cast<const uint64_t*>(stream_in), stream_q, n_cw, out);
     } else {

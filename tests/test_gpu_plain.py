@@ -409,3 +409,23 @@ def test_decode_either_side_of_the_cached_size(gpu_device, r):
         assert np.array_equal(e[first:first + 128].cpu().numpy(), e_ref)
     d_ref, e_ref = oracle.decode(cw[(n - 63) * wpc:].cpu().numpy().view(np.uint64), r)
     assert np.array_equal(e1[n - 63:].cpu().numpy(), e_ref)
+
+
+@pytest.mark.parametrize("n_cw", [1023, 1024, 1025, 41297762, 41297763])
+def test_encode_hamming_31_26_tiles_and_long_streams(gpu_device, n_cw):
+    """Hamming(31,26) at an odd output word around a tile of 1024 codewords, and
+    around a message stream of 128 MiB: the head, slices and the tail against the
+    oracle, the words around the output untouched."""
+    import torch
+
+    stream = synth.message_stream_torch(synth.workload_seed("gpu-enc-31-26", n_cw), n_cw, 5, gpu_device)
+    buf = torch.full((n_cw + 2,), 0x5A5A5A5A5A5A5A5A, dtype=torch.int64, device=gpu_device)
+    hm.hamming_encode(stream, n_cw, 5, buf[1:1 + n_cw])
+    torch.cuda.synchronize()
+    ends = buf[[0, -1]].cpu().numpy().view(np.uint64)
+    assert (ends == 0x5A5A5A5A5A5A5A5A).all()
+    for first in {0, n_cw // 3 // 64 * 64, max(0, (n_cw - 3000) // 64 * 64)}:
+        n = min(3100, n_cw - first)
+        words = stream[first * 26 // 64:][:(n * 26 + 63) // 64].cpu().numpy().view(np.uint64)
+        got = buf[1 + first:1 + first + n].cpu().numpy().view(np.uint64)
+        assert np.array_equal(got, oracle.encode(words, n, 5)), first
