@@ -180,12 +180,12 @@ int batch_prepare(const uint64_t* cw_arena, uint64_t cw_words, const hamming_pac
     *grid = uint32_t(blocks);
     a.blocks = batch_grid_blocks(cw_words, max_packets, max_codewords, 0, a.chunk_log2, schedule);
     // the fine map has at most one entry per chunk of the bound, and a block of
-    // its kernel fills 1024 (it loops, so this only sizes its grid)
+    // its kernel fills 256 (it loops, so this only sizes its grid)
     const uint64_t chunks =
         (batch_tile_bound(cw_words, max_packets, max_codewords, schedule) + (uint64_t(1) << a.chunk_log2) - 1) >>
         a.chunk_log2;
     const uint64_t fine_entries = chunks < a.fine_cap ? chunks : a.fine_cap;
-    a.fine_blocks = uint32_t((fine_entries + 1023) / 1024);
+    a.fine_blocks = uint32_t((fine_entries + 255) / 256);
     return HAMMING_OK;
 }
 
