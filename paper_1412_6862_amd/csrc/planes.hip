@@ -340,26 +340,40 @@ __global__ __launch_bounds__(64 * kToPlanesWaves) void to_planes_kernel(const ui
     if (wave * kToPlanesCw >= n_cw) return;
     uint32_t* buf = reinterpret_cast<uint32_t*>(&lds_raw[wib][0]);
 
+    // All loads are in flight before the first is used.  A check of its own per
+    // vector made each wait for the one before (2^18 codewords of r = 5 from HBM 10.2 us
+    // against 4.3; 2^22 13.3 against 11.2).
     uint32_t in[NV][PER][ND];
-    const u32x4a8* src = reinterpret_cast<const u32x4a8*>(cw + wave * kToPlanesCw * WPC) + lane;
+    const uint64_t* words = cw + wave * kToPlanesCw * WPC;
     const uint64_t rem = (n_cw - wave * kToPlanesCw) * WPC;      // input words left
-    const bool full = rem >= uint64_t(kToPlanesCw) * WPC;
+    u32x4 x[NV];
+    if (rem >= uint64_t(kToPlanesCw) * WPC) {
+        const u32x4a8* src = reinterpret_cast<const u32x4a8*>(words) + lane;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        u32x4 x = {0u, 0u, 0u, 0u};
-        const uint64_t w = 2 * (64u * uint64_t(v) + lane);       // first word of this lane's vector v
-        if (full || w + 1 < rem) {
-            x = __builtin_nontemporal_load(src + 64 * v);
-        } else if (w < rem) {
-            const uint64_t y = reinterpret_cast<const uint64_t*>(src + 64 * v)[0];
-            x.x = uint32_t(y);
-            x.y = uint32_t(y >> 32);
+        for (int v = 0; v < NV; ++v) x[v] = __builtin_nontemporal_load(src + 64 * v);
+    } else {
+        // words past the last one are read as the last one, and zeroed
+        const uint32_t last = uint32_t(rem) - 1u;
+        uint64_t y[NV][2];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const uint32_t w = 2u * (64u * v + lane);            // first word of this lane's vector v
+            y[v][0] = words[min(w, last)];
+            y[v][1] = words[min(w + 1u, last)];
         }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const uint32_t w = 2u * (64u * v + lane);
+            const uint64_t lo = w <= last ? y[v][0] : 0, hi = w + 1u <= last ? y[v][1] : 0;
+            x[v] = u32x4{uint32_t(lo), uint32_t(lo >> 32), uint32_t(hi), uint32_t(hi >> 32)};
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
         for (int c = 0; c < PER; ++c)
 #pragma unroll
-            for (int d = 0; d < ND; ++d) in[v][c][d] = x[c * 2 * WPC + d];
-    }
+            for (int d = 0; d < ND; ++d) in[v][c][d] = x[v][c * 2 * WPC + d];
 
     const uint64_t g = wave * 64 + lane;
     const bool stores = 32 * g < n_cw;
