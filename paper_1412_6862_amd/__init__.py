@@ -16,6 +16,7 @@ import ctypes
 import os
 import threading
 import time
+from operator import index as _index
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libhamming.so")
@@ -182,13 +183,21 @@ def _current_stream() -> int:
         return torch.cuda.current_stream().cuda_stream
 
 
+_MESSAGE_BITS = (0, 0, 0, 4, 11, 26, 57, 120) + (0,) * 8       # by r; -8..-1 and 8..15 are 0
+
+
 def _message_stream_bytes(n_cw: int, r: int) -> int:
     """``hamming_data_bytes``, the bytes that the library writes, without a
-    foreign call where plain integers in range allow it.  Other integer types
-    go through the library: numpy's would wrap at their own width, and the
-    tensor would be shorter than what is written to it."""
-    if type(n_cw) is int and type(r) is int and 3 <= r <= 7 and 0 <= n_cw <= HAMMING_MAX_CODEWORDS:
-        return (n_cw * ((1 << r) - 1 - r) + 63) // 64 * 8
+    foreign call where r and n_cw are in range.  The product is one of Python
+    integers: numpy's would wrap at their own width, and the tensor would be
+    shorter than what is written to it."""
+    n = _index(n_cw)
+    try:
+        k = _MESSAGE_BITS[r]
+    except IndexError:
+        k = 0
+    if k and 0 <= n <= HAMMING_MAX_CODEWORDS:
+        return (n * k + 63) // 64 * 8
     return hamming_data_bytes(n_cw, r)
 
 
