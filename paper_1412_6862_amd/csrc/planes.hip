@@ -100,13 +100,15 @@ __device__ __forceinline__ void transpose32(uint32_t* A)
 constexpr uint32_t kPlanesXcdChunk = 16;
 
 // Planes of at most this many bytes are read with ordinary loads, larger ones
-// with nontemporal loads.  Planes are usually decoded right after they were
-// written, and up to a quarter of the 256 MB Infinity Cache they are still
-// there: r = 5, 2^24 codewords (62 MiB) 22.4 against 26-27 us, r = 3, 2^26
-// codewords (56 MiB) 24.4 against 28 us.  When they are not, ordinary loads
-// cost 0-8% at these sizes (27.4 against 26.6 us, 30.8 against 28.6 us);
-// beyond, nontemporal ones are 3-10% faster either way (r = 6, 2^24: 48
-// against 52-55 us).
+// with nontemporal loads.  Off whole 128-byte lines two waves share the lines at the
+// ends of their pieces, and the caches answer the second (32 MiB of planes just
+// written, ordinary against nontemporal loads: r = 4 13.9 against 17.7 us, r = 5 12.9
+// against 17.4; from HBM 16.9 against 17.6 and 16.1 either way).  On whole lines
+// planes decoded again come out of the Infinity Cache (r = 5 9.8 against 14.7, r = 6
+// 11.6 against 15.4), from HBM r = 3 takes 14.5 against 18.2 and the others the same
+// within 3%, but just written they take longer (r = 3 14.3 against 11.2, r = 4 13.7
+// against 13.0, r = 5 12.2 against 11.4, r = 6 13.7 against 13.0).  Beyond, nontemporal
+// ones are 3-10% faster either way (r = 6, 2^24 codewords: 48 against 52-55 us).
 constexpr uint64_t kPlanesCachedBytes = uint64_t(64) << 20;
 
 template <int R, bool NT>
@@ -311,7 +313,7 @@ __global__ __launch_bounds__(64 * PlaneShape<R>::WAVES) void decode_planes_kerne
 // Bound by HBM.  The first form (a lane loading its 32 codewords itself, 4
 // bytes at a 256-byte lane stride) spent its time on the 64 cache lines that
 // each load touched: 82 us (r = 5) and 130 us (r = 6) for 2^24 codewords,
-// against 40 and 47 us now (5.0 and 5.6 TB/s).  Consecutive blocks go to one
+// against 35 and 46 us now (5.7 TB/s).  Consecutive blocks go to one
 // XCD in slices of 32 (1: 3-8% slower at 2^24 codewords, equal at 2^26).
 //
 // NT: nontemporal plane stores.  They are 4-7% faster when every plane starts
