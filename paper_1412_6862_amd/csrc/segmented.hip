@@ -1063,15 +1063,17 @@ __global__ __launch_bounds__(64 * kSegWaves) void seg_encode_kernel(SegArgs a)
 constexpr uint32_t kWideMaxPackets = 2048;
 std::atomic<uint32_t> g_seg_threads{0};
 
-uint32_t auto_threads_per_packet(uint32_t n_packets, uint32_t max_msg_bytes, bool decode)
+uint32_t auto_threads_per_packet(uint32_t n_packets, uint32_t max_msg_bytes)
 {
     if (n_packets <= kWideMaxPackets) return 256;
-    // 8 lanes share the per-packet work between eight packets of a wave, 16
-    // have fewer windows each.  2^19 equal packets, 8 against 16: decode 500
-    // bytes 105-113 against 119 us, 640 bytes 130-134 against 121-124; encode
-    // 640 bytes 127 against 141 us, 800 bytes 176-180 against 158-161.  From
-    // there 16 win up to 2000 bytes (339 us, 32: 344) for every t
-    if (max_msg_bytes <= (decode ? 640u : 704u)) return 8u;
+    // 8 lanes share the per-packet work between eight packets of a wave, 16 have
+    // fewer windows each.  Up to 633 bytes 8 are faster (from 16384 packets on; 2^17
+    // equal packets of 560 bytes, 16 against 8, mean of t = 2 to 6: decode 1.16 times
+    // as long, encode 1.09; 633 bytes 1.07 and 1.08), from 634 on, where parts of t = 5
+    // have nine windows on 8 lanes, 16 (640 bytes 0.96 and 0.99, 700 bytes 0.91 and 0.93;
+    // 2100 packets of 640 bytes 0.79 and 0.78; slower only at 32768 packets, encoding,
+    // by 2-9%).  They win up to 2000 bytes (2^19 packets 339 us, 32: 344) for every t
+    if (max_msg_bytes <= 633u) return 8u;
     // Up to 4096 packets 16 lanes each leave a SIMD one wave, 32 two.  Decode
     // and encode, 32 against 16: 4096 equal packets of 2000 bytes 6.8 and 7.0
     // against 7.9 and 7.7 us, 400..2000 bytes 7.3 and 8.1 against 8.4 and 9.4;
@@ -1097,9 +1099,9 @@ uint32_t part_slot_dwords(uint32_t max_msg_bytes, uint32_t group, uint32_t slice
 // The kernel for GROUP lanes per packet, with registers for 8 (encoding 9: the
 // compiler then needs 65 registers, with 8 it takes 86), 12 or 15 windows in a lane.
 // A lane's share is max_msg_bytes / (16 GROUP) windows if all lanes have one; the
-// largest share of t <= 8 segments is about 1.5 times that.  Decoding with 8 lanes,
-// t = 5 has nine windows from 634 bytes on (2^18 packets of 634 bytes 86 -> 76 us; the
-// other t 1-3% slower than with 8).  On 16 lanes t = 9 and 10 have more than 12 from
+// largest share of t <= 8 segments is about 1.5 times that.  Where the caller sets 8
+// lanes, t = 5 has nine windows from 634 bytes on (2^18 packets of 634 bytes, decode 76
+// us, 86 in the window form).  On 16 lanes t = 9 and 10 have more than 12 from
 // 1715 bytes on (2000 bytes, t = 10, decode 253 us in the window form, 180 with 15
 // windows, t = 9 229 and 180; t <= 6 0-1% slower than with 12).
 // The window form loads 2 windows ahead while a thread has about five of them
@@ -1145,7 +1147,7 @@ void launch(const SegArgs& a0, uint32_t n_packets, uint32_t max_msg_bytes, hipSt
     SegArgs a = a0;
     a.cached = uint64_t(n_packets) * max_msg_bytes <= kSegCachedBytes ? 1u : 0u;
     uint32_t group = g_seg_threads.load();
-    if (group == 0) group = auto_threads_per_packet(n_packets, max_msg_bytes, DECODE);
+    if (group == 0) group = auto_threads_per_packet(n_packets, max_msg_bytes);
     const uint32_t per_block = 64 * kSegWaves / group;
     void (*kernel)(SegArgs);
     size_t lds;

@@ -564,3 +564,10 @@ def test_segmented_longest_parts(gpu_device, seg_mode, msg_bytes, t):
     """Parts of 8 and 9, and of up to 15 windows, where the part form's kernels
     have registers for one more or one less."""
     test_segmented_equal_packets_at_a_stride(gpu_device, seg_mode, msg_bytes, t, 0)
+
+
+@pytest.mark.parametrize("msg_bytes", [633, 634, 704, 705])
+def test_segmented_automatic_lanes_of_middling_packets(gpu_device, msg_bytes):
+    """Both directions on either side of the bound from 8 to 16 lanes, and of
+    where it lay for the encoder before."""
+    test_segmented_automatic_group_edges(gpu_device, 2049, msg_bytes)
