@@ -226,23 +226,27 @@ __device__ __forceinline__ uint32_t wave_search_packet(const uint64_t* ts, uint3
     return lo;
 }
 
-// The fine map, 64 consecutive entries per wave, one per lane: the packets of the
-// first and the last of them bound a short binary search for every entry.  With 256
-// entries per wave a lane's four searches ran one after another (2000 packets, 2 MB:
-// the decode 20.5 us against 15.8, 17.6 with a coarse map in a launch of its own;
-// 20000, 200 MB 120.6, 118.3 and 125.5).
+// The fine map, 64 or 256 consecutive entries per wave: the packets of the first
+// and the last of them bound a short binary search for every entry.  Small maps take
+// one entry per lane, since a lane's four searches run one after another (2000
+// packets, 2 MB: the decode 15.8 against 20.5 us, 17.6 with a coarse map in a launch
+// of its own; 20000, 200 MB 118.3, 120.6 and 125.5).  Above kFineLaneEntries the
+// waves' own two searches cost more than that: this kernel, 64 against 256 per wave,
+// 2000 packets 5.2 and 5.6 us at 0.4 M entries, 7.4 and 5.6 at 0.8 M; 20000 packets
+// 5.8 and 7.1, 8.2 and 7.5, at 4 M 30.5 and 16.9.
+constexpr uint64_t kFineLaneEntries = uint64_t(1) << 19;
 __global__ __launch_bounds__(256) void batch_fine_kernel(BatchArgs a)
 {
     const uint64_t n_fine = a.ws->n_fine;
     const uint32_t g = a.ws->fine_log2, n = uint32_t(a.ws->n_packets), lane = threadIdx.x & 63u;
-    const uint64_t step = uint64_t(gridDim.x) * 256;
-    for (uint64_t first = uint64_t(blockIdx.x) * 256 + __builtin_amdgcn_readfirstlane(threadIdx.x & ~63u);
+    const uint32_t per_wave = n_fine > kFineLaneEntries ? 256u : 64u;
+    const uint64_t step = uint64_t(gridDim.x) * 4 * per_wave;
+    for (uint64_t first = (uint64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * per_wave;
          first < n_fine; first += step) {
-        const uint64_t last = (first + 64 < n_fine ? first + 64 : n_fine) - 1;
+        const uint64_t end = first + per_wave < n_fine ? first + per_wave : n_fine;
         const uint32_t lo = wave_search_packet(a.tile_start, n, first << g);
-        const uint32_t hi = wave_search_packet(a.tile_start, n, last << g) + 1u;
-        const uint64_t j = first + lane;
-        if (j <= last) a.fine[j] = search_packet(a.tile_start, j << g, lo, hi);
+        const uint32_t hi = wave_search_packet(a.tile_start, n, (end - 1) << g) + 1u;
+        for (uint64_t j = first + lane; j < end; j += 64) a.fine[j] = search_packet(a.tile_start, j << g, lo, hi);
     }
 }
 

@@ -7,6 +7,7 @@ map in the two-launch form, the fine map in the three-launch form)."""
 import numpy as np
 import pytest
 
+import oracle
 import paper_1412_6862_amd as hm
 from test_gpu_batch import _build_batch, _check_outputs, _expect, _to_dev
 
@@ -128,6 +129,28 @@ def test_three_launches_many_tiny_and_empty_packets(gpu_device, config, schedule
     assert ((t["tiles"] >> t["fine_log2"]) == 0) == bool(one_entry)
     assert not bd.status.cpu().numpy().any()
     _check_outputs(bd, descs, _expect(ys, descs), data_fill=0x77, ep_fill=0x88)
+
+
+@pytest.mark.parametrize("n_packets", [1 << 19, (1 << 19) + 1, (1 << 19) + 257, (1 << 19) + 4099])
+def test_three_launches_map_of_many_entries(gpu_device, config, n_packets):
+    """A packet of one (63,57) codeword per fine-map entry, either side of the
+    map size from which a wave fills 256 entries."""
+    rng = np.random.default_rng(n_packets)
+    cw = rng.integers(0, 1 << 63, n_packets, dtype=np.uint64)
+    data, errpos = oracle.decode(cw, 6)
+    bits = np.unpackbits(data.view(np.uint8), bitorder="little")[:n_packets * 57].reshape(n_packets, 57)
+    want = np.packbits(np.pad(bits, ((0, 0), (0, 7))), axis=1, bitorder="little").view(np.uint64)[:, 0]
+    descs = np.zeros(n_packets, dtype=hm.packet_dtype())
+    descs["in_word_off"], descs["n_cw"], descs["r"] = np.arange(n_packets), 1, 6
+    config(chunk_log2=0)
+    bd = hm.BatchDecoder(_to_dev(cw, gpu_device), n_packets)
+    bd.set_packets(descs)
+    _decode(bd)
+    t = bd.totals()
+    assert t["tiles"] == n_packets and t["fine_log2"] == 0 and not bd.status.cpu().numpy().any()
+    got = bd.data.cpu().numpy().view(np.uint64)[descs["data_word_off"].astype(np.int64)]
+    assert np.array_equal(got, want)
+    assert np.array_equal(bd.errpos.cpu().numpy()[descs["errpos_off"].astype(np.int64)], errpos)
 
 
 @pytest.mark.parametrize("one_entry", [0, 1])
