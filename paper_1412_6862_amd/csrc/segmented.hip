@@ -5,9 +5,10 @@
 // segment is the XOR over its index sets (Sec. III.A, III.C, Algorithm 1).
 //
 // A group of threads per packet (part of a wave, a wave or a workgroup), in one
-// of two forms.  A wave whose packets have one shape and lie at one stride takes
-// the part form (below, at its kernels); everything else, and the workgroup
-// per packet, takes the window form:
+// of two forms.  A wave whose packets lie end to end (of one shape or of several),
+// or of one shape at one stride, takes the part form (below, at its kernels);
+// every other wave, batches of packets under 192 bytes and the workgroup per packet
+// take the window form:
 //
 // The 128-position windows of all segments form one flat list dealt to the
 // threads.  Decoding, a thread reads each of its windows once from HBM (an
@@ -1132,11 +1133,13 @@ constexpr void (*window_kernel())(SegArgs)
 }
 
 // Batches of at most this many message bytes are read with ordinary loads,
-// larger ones with nontemporal loads.  Packets are usually decoded soon after
-// they were written, and half the 256 MB Infinity Cache can still hold them:
-// 2^16 packets of 1200 bytes 28 against 31 us, of 2000 bytes 43 against 48 us.
-// 2^19 packets, which it cannot hold, take 2-3% longer that way (1200 bytes
-// 224 against 219 us, 2000 bytes 345 against 339 us).
+// larger ones with nontemporal loads; half the 256 MB Infinity Cache can still
+// hold them.  Decoding, ordinary against nontemporal loads by where the batch lies:
+// read before (2^16 packets of 1200 bytes 28 against 31 us, of 2000 bytes 43
+// against 48 us), written by a copy just before (25.7 against 23.8 and 48.0 against
+// 41.0 us), written by the encoder just before or in HBM (equal within 3%).  2^19
+// packets, which the cache cannot hold, take 2-3% longer with ordinary loads (1200
+// bytes 224 against 219 us, 2000 bytes 345 against 339 us).
 constexpr uint64_t kSegCachedBytes = uint64_t(128) << 20;
 
 // Launches the decode or encode of n_packets with the configured (or
