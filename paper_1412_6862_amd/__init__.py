@@ -482,7 +482,8 @@ def encode(messages, n_cw: int, r: int, stream=None):
 
     if not messages.is_cuda:
         raise ValueError("messages must be a device tensor")
-    out = torch.empty(n_cw * words_per_codeword(r), dtype=torch.int64, device=messages.device)
+    # a product of Python integers, as in _message_stream_bytes
+    out = torch.empty(_index(n_cw) * words_per_codeword(r), dtype=torch.int64, device=messages.device)
     hamming_encode(messages.contiguous(), n_cw, r, out, stream)
     return out
 

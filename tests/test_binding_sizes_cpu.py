@@ -2,6 +2,8 @@
 ``decode_planes`` and ``Server.result`` size for a call has exactly the bytes
 that the library writes (``hamming_data_bytes``), for every integer type that
 the entry points take and past the ends of their ranges."""
+import types
+
 import numpy as np
 import pytest
 
@@ -22,3 +24,13 @@ def test_message_stream_bytes_is_what_the_library_writes(kind):
             got = hm._message_stream_bytes(kind(n), r)
             assert got == want and type(got) is int, (n, r)
             assert hm._message_stream_bytes(kind(n), kind(r)) == want, (n, r)
+
+
+@pytest.mark.parametrize("kind,n_cw", [(np.int8, 127), (np.uint8, 200), (np.int32, 1000), (np.uint64, 1000), (int, 1000)])
+@pytest.mark.parametrize("r", [3, 6, 7])
+def test_encode_allocates_every_codeword(monkeypatch, kind, n_cw, r):
+    got = {}
+    messages = types.SimpleNamespace(is_cuda=True, device="cpu", contiguous=lambda: None)
+    monkeypatch.setattr(hm, "hamming_encode", lambda msg, n, r, out, stream=None: got.update(n=int(n), out=out))
+    out = hm.encode(messages, kind(n_cw), r)
+    assert out is got["out"] and got["n"] == n_cw and out.numel() == n_cw * (2 if r == 7 else 1)
