@@ -367,7 +367,7 @@ def to_planes(codewords, r: int, stream=None):
     cw = codewords.contiguous()
     n_cw = cw.numel() // words_per_codeword(r)
     pw = (n_cw + 63) // 64
-    planes = torch.empty(((1 << r) - 1) * pw, dtype=torch.int64, device=cw.device)
+    planes = torch.empty(((1 << _index(r)) - 1) * pw, dtype=torch.int64, device=cw.device)
     if (n_cw + 31) // 32 % 2:       # the converter writes half of each plane's last word
         with _on_stream(stream, cw.device):
             planes.view(-1, pw)[:, -1].zero_()

@@ -6,6 +6,7 @@ import types
 
 import numpy as np
 import pytest
+import torch
 
 import paper_1412_6862_amd as hm
 
@@ -34,3 +35,12 @@ def test_encode_allocates_every_codeword(monkeypatch, kind, n_cw, r):
     monkeypatch.setattr(hm, "hamming_encode", lambda msg, n, r, out, stream=None: got.update(n=int(n), out=out))
     out = hm.encode(messages, kind(n_cw), r)
     assert out is got["out"] and got["n"] == n_cw and out.numel() == n_cw * (2 if r == 7 else 1)
+
+
+@pytest.mark.parametrize("kind", [int, np.int8, np.uint8, np.int32, np.uint64])
+@pytest.mark.parametrize("r", [3, 6, 7])
+def test_to_planes_allocates_every_plane(monkeypatch, kind, r):
+    monkeypatch.setattr(hm, "hamming_to_planes", lambda cw, n, r, planes, pw, stream=None: None)
+    n_cw = 640
+    planes, pw = hm.to_planes(torch.zeros(n_cw * (2 if r == 7 else 1), dtype=torch.int64), kind(r))
+    assert pw == 10 and planes.numel() == ((1 << r) - 1) * 10
