@@ -715,7 +715,7 @@ class Server:
     def result(self, completion, r: int, n_cw: int):
         """(data, errpos) device views of a completed request's outputs."""
         d, e = completion.data_offset, completion.errpos_offset
-        return self.output[d:d + _message_stream_bytes(n_cw, r)], self.output[e:e + n_cw]
+        return self.output[d:d + _message_stream_bytes(n_cw, r)], self.output[e:e + _index(n_cw)]
 
     def submit(self, in_word_off: int, n_cw: int, r: int, arrival_ns: int | None = None) -> int:
         # time.monotonic_ns reads the clock of hamming_server_now_ns

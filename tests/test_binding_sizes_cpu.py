@@ -44,3 +44,10 @@ def test_to_planes_allocates_every_plane(monkeypatch, kind, r):
     n_cw = 640
     planes, pw = hm.to_planes(torch.zeros(n_cw * (2 if r == 7 else 1), dtype=torch.int64), kind(r))
     assert pw == 10 and planes.numel() == ((1 << r) - 1) * 10
+
+
+@pytest.mark.parametrize("kind", [int, np.int8, np.uint8, np.int32, np.uint64])
+def test_server_result_views(kind):
+    server = types.SimpleNamespace(output=torch.arange(2000) % 251)
+    data, errpos = hm.Server.result(server, types.SimpleNamespace(data_offset=16, errpos_offset=240), 6, kind(100))
+    assert torch.equal(data, server.output[16:16 + 720]) and torch.equal(errpos, server.output[240:340])
