@@ -191,14 +191,18 @@ def _message_stream_bytes(n_cw: int, r: int) -> int:
     foreign call where r and n_cw are in range.  The product is one of Python
     integers: numpy's would wrap at their own width, and the tensor would be
     shorter than what is written to it."""
-    n = _index(n_cw)
+    return _stream_bytes(_index(n_cw), r)
+
+
+def _stream_bytes(n: int, r: int) -> int:
+    """The same for a count that is a Python integer already."""
     try:
         k = _MESSAGE_BITS[r]
     except IndexError:
         k = 0
     if k and 0 <= n <= HAMMING_MAX_CODEWORDS:
         return (n * k + 63) // 64 * 8
-    return hamming_data_bytes(n_cw, r)
+    return hamming_data_bytes(n, r)
 
 
 def _ptr(t) -> int:
@@ -468,7 +472,7 @@ def decode(codewords, r: int, errpos: bool = True, stream=None):
             raise ValueError("codeword tensor length is not a multiple of the words per codeword")
         n_cw //= 2
     dev = cw.device
-    data = torch.empty(_message_stream_bytes(n_cw, r), dtype=torch.uint8, device=dev)
+    data = torch.empty(_stream_bytes(n_cw, r), dtype=torch.uint8, device=dev)
     ep = torch.empty(n_cw, dtype=torch.uint8, device=dev) if errpos else None
     _check(library().hamming_decode(cw.data_ptr(), n_cw, r, data.data_ptr(), ep.data_ptr() if errpos else 0,
                                     _stream(stream)), "hamming_decode")
@@ -715,7 +719,8 @@ class Server:
     def result(self, completion, r: int, n_cw: int):
         """(data, errpos) device views of a completed request's outputs."""
         d, e = completion.data_offset, completion.errpos_offset
-        return self.output[d:d + _message_stream_bytes(n_cw, r)], self.output[e:e + _index(n_cw)]
+        n = _index(n_cw)
+        return self.output[d:d + _stream_bytes(n, r)], self.output[e:e + n]
 
     def submit(self, in_word_off: int, n_cw: int, r: int, arrival_ns: int | None = None) -> int:
         # time.monotonic_ns reads the clock of hamming_server_now_ns
